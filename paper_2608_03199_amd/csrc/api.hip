@@ -99,7 +99,16 @@ struct sieve_index {
   void* centroids = nullptr;
   void* cfrag = nullptr;  // fragment-order centroids (ranking), or null
   void* vfrag = nullptr;  // fragment-order vectors (scan), or null
-  int64_t* foff = nullptr;  // [nlist + 1] partition starts in vfrag (rows)
+  int64_t* foff = nullptr;  // [nlist + 1] partition starts in vfrag and v8 (rows)
+  // 8-bit rows in fragment order with their lists' parameters (screened
+  // scan), or null
+  void* v8 = nullptr;
+  ScreenParam* lpar = nullptr;
+  // for the estimate of the pairs that pass the screen: its usual slack (twice
+  // the lists' mean err times their mean norm) and the scores of sampled row
+  // pairs of one list, ascending
+  double scr_slack = 0.0;
+  std::vector<float> scr_scores;
   std::vector<int64_t> h_offsets;
   int64_t max_list = 0;
   double cmax = 0.0;
@@ -110,7 +119,7 @@ struct sieve_index {
   X(state_a) X(state_b) X(lmax) X(hcount) X(hoff) X(hcur) X(scan_tmp) X(pool)              \
   X(pool_sorted) X(heavy) X(spill) X(have) X(ext) X(qext) X(Pext) X(cand) X(ccount) X(cal_idx)      \
   X(cal_q) X(cal_x) X(cal_bits) X(cal_rank) X(cal_hist) X(mix_ids) X(mix_scores)            \
-  X(mix_probes) X(spec_bits) X(rlog)
+  X(mix_probes) X(spec_bits) X(rlog) X(q8) X(qpar)
 #define SIEVE_DECLARE_BUF(name) Buf name;
   SIEVE_WORKSPACE(SIEVE_DECLARE_BUF)
 #undef SIEVE_DECLARE_BUF
@@ -134,12 +143,30 @@ struct sieve_index {
 
 namespace {
 
+// The same for a workspace buffer of an index.  Where device memory runs out
+// the index gives its 8-bit copy back and goes on with exact scans: a search
+// needs no more memory than without the copy.  (hipFree waits for the device.)
+int ensure(sieve_index* ix, Buf& b, size_t bytes) {
+  int st = ensure(b, bytes);
+  if (st != SIEVE_ENOMEM || !ix->v8 || getenv("SIEVE_ALLOC_CAP")) return st;
+  for (void* p : {ix->v8, (void*)ix->lpar, ix->q8.p, ix->qpar.p})
+    if (p) (void)hipFree(p);
+  ix->v8 = nullptr;
+  ix->lpar = nullptr;
+  ix->q8 = ix->qpar = Buf{};
+  return ensure(b, bytes);
+}
+
 int elem_bytes(int dtype) { return dtype == SIEVE_F32 ? 4 : 2; }
 
 double host_elem(const void* base, int dtype, int64_t i) {
   if (dtype == SIEVE_F32) return (double)((const float*)base)[i];
   return (double)((const _Float16*)base)[i];
 }
+
+// Rounds of a search are screened while fewer than 1 / kScreenPassInv of
+// their (query, row) pairs pass.
+constexpr unsigned long long kScreenPassInv = 40;
 
 enum Phase { kRank = 0, kSched, kScan, kUpdate, kFinal, kTotal, kPhases };
 
@@ -271,6 +298,9 @@ struct SearchPlan {
   int spec_max;        // ranks issued past the stop line, at most
   int spec_min;        // a line must move at least this far to speculate
   int hit_words;       // 32-bit words per query of the rank bitmap (spec)
+  bool screen;         // screened scans (screen_tile.h)
+  int s_chunk;         // rows per tile in their sparse rounds
+  int s_chunk_dense;   // and in their dense rounds
 };
 
 int check_common(const sieve_index* ix, const void* queries, int64_t nq, int32_t k, float tau,
@@ -305,31 +335,35 @@ int grow_workspace(sieve_index* ix, const SearchPlan& pl) {
   const int n = pl.n;
   const int64_t rank_rows = pl.mode == 2 ? pl.fix_chunk : nq;
   int st;
-  if ((st = ensure(ix->scores, (size_t)pl.rank_chunk * ix->nlist * sizeof(float)))) return st;
-  if ((st = ensure(ix->P, (size_t)rank_rows * n * sizeof(int32_t)))) return st;
-  if ((st = ensure(ix->items, (size_t)pl.item_cap * sizeof(Item)))) return st;
-  if ((st = ensure(ix->bucket, (size_t)pl.item_cap * sizeof(BItem)))) return st;
+  if ((st = ensure(ix, ix->scores, (size_t)pl.rank_chunk * ix->nlist * sizeof(float)))) return st;
+  if ((st = ensure(ix, ix->P, (size_t)rank_rows * n * sizeof(int32_t)))) return st;
+  if ((st = ensure(ix, ix->items, (size_t)pl.item_cap * sizeof(Item)))) return st;
+  if ((st = ensure(ix, ix->bucket, (size_t)pl.item_cap * sizeof(BItem)))) return st;
   // tiles: sum_p ceil(c_p / tq) * ceil(len_p / rc) <= items * max_chunks / tq + lists + rows / rc
-  const int64_t max_ch = (ix->max_list + pl.row_chunk - 1) / pl.row_chunk;
+  const int chunk = pl.screen ? std::min(pl.row_chunk, pl.s_chunk) : pl.row_chunk;
+  const int64_t max_ch = (ix->max_list + chunk - 1) / chunk;
   const int64_t tile_cap = pl.item_cap / std::min(pl.group_q, pl.min_group) *
                                (max_ch > 0 ? max_ch : 1) +
-                           ix->nlist + ix->n / pl.row_chunk + 16;
+                           ix->nlist + ix->n / chunk + 16;
   if (tile_cap > INT32_MAX) return fail(SIEVE_EUNSUPPORTED, "tile count bound overflows int32");
-  if ((st = ensure(ix->tiles, (size_t)tile_cap * sizeof(Tile)))) return st;
+  if ((st = ensure(ix, ix->tiles, (size_t)tile_cap * sizeof(Tile)))) return st;
   const size_t nl = (size_t)ix->nlist;
-  if ((st = ensure(ix->cnt, nl * 4)) || (st = ensure(ix->item_off, nl * 4)) ||
-      (st = ensure(ix->cursor, nl * 4)) || (st = ensure(ix->tile_off, nl * 4)))
+  if ((st = ensure(ix, ix->cnt, nl * 4)) || (st = ensure(ix, ix->item_off, nl * 4)) ||
+      (st = ensure(ix, ix->cursor, nl * 4)) || (st = ensure(ix, ix->tile_off, nl * 4)))
     return st;
-  if ((st = ensure(ix->rc, sizeof(RoundCounters)))) return st;
+  if ((st = ensure(ix, ix->rc, sizeof(RoundCounters)))) return st;
   const size_t qn = (size_t)nq * 4;
-  if ((st = ensure(ix->have, qn)) || (st = ensure(ix->ext, qn))) return st;
-  if ((st = ensure(ix->state_a, qn)) || (st = ensure(ix->state_b, qn)) ||
-      (st = ensure(ix->lmax, qn)) || (st = ensure(ix->hcount, qn)) ||
-      (st = ensure(ix->hoff, (size_t)nq * 8)) || (st = ensure(ix->hcur, (size_t)nq * 8)))
+  if ((st = ensure(ix, ix->have, qn)) || (st = ensure(ix, ix->ext, qn))) return st;
+  if ((st = ensure(ix, ix->state_a, qn)) || (st = ensure(ix, ix->state_b, qn)) ||
+      (st = ensure(ix, ix->lmax, qn)) || (st = ensure(ix, ix->hcount, qn)) ||
+      (st = ensure(ix, ix->hoff, (size_t)nq * 8)) || (st = ensure(ix, ix->hcur, (size_t)nq * 8)))
     return st;
-  if ((st = ensure(ix->scan_tmp, exclusive_scan_tmp_elems(nq) * 8))) return st;
-  if (pl.spec && (st = ensure(ix->spec_bits, (size_t)nq * pl.hit_words * 4))) return st;
-  if ((st = ensure(ix->rlog, (size_t)kMaxLogRounds * sizeof(RoundSnap)))) return st;
+  if ((st = ensure(ix, ix->scan_tmp, exclusive_scan_tmp_elems(nq) * 8))) return st;
+  if (pl.spec && (st = ensure(ix, ix->spec_bits, (size_t)nq * pl.hit_words * 4))) return st;
+  if (pl.screen && ((st = ensure(ix, ix->q8, (size_t)nq * screen_chunks(ix->d) * 64)) ||
+                    (st = ensure(ix, ix->qpar, (size_t)nq * sizeof(ScreenParam)))))
+    return st;
+  if ((st = ensure(ix, ix->rlog, (size_t)kMaxLogRounds * sizeof(RoundSnap)))) return st;
   // The pool holds at most k entries per (query, tile); most searches need far
   // fewer, so it starts small and grows (the search is then re-run) only when
   // a search needs more.
@@ -341,15 +375,15 @@ int grow_workspace(sieve_index* ix, const SearchPlan& pl) {
   // regrowth), then grown on demand
   if (ix->heavy_cap == 0)
     ix->heavy_cap = env_int("SIEVE_HEAVY_CAP0", (int)std::min<int64_t>(std::max<int64_t>(4096, nq / 8), 1 << 24));
-  if ((st = ensure(ix->heavy, (size_t)ix->heavy_cap * sizeof(HeavyRec)))) return st;
+  if ((st = ensure(ix, ix->heavy, (size_t)ix->heavy_cap * sizeof(HeavyRec)))) return st;
   // per scan work-group: the candidate arena's global extension and the
   // tile's grouped arena (every grid of this search has at most spill_grid
   // work-groups)
-  if ((st = ensure(ix->spill,
+  if ((st = ensure(ix, ix->spill,
                    (size_t)spill_grid(ix) * arena_block_entries(spill_cap(ix)) * sizeof(TileSpill))))
     return st;
-  if ((st = ensure(ix->pool, (size_t)ix->pool_cap * sizeof(Hit)))) return st;
-  if ((st = ensure(ix->pool_sorted, (size_t)ix->pool_cap * sizeof(Hit)))) return st;
+  if ((st = ensure(ix, ix->pool, (size_t)ix->pool_cap * sizeof(Hit)))) return st;
+  if ((st = ensure(ix, ix->pool_sorted, (size_t)ix->pool_cap * sizeof(Hit)))) return st;
   if (!ix->rc_host) HIP_TRY(hipHostMalloc((void**)&ix->rc_host, sizeof(RoundCounters), 0));
   if (!ix->rs_host) {
     HIP_TRY(hipHostMalloc((void**)&ix->rs_host, sizeof(RoundSummary),
@@ -407,8 +441,8 @@ int rank_queries(sieve_index* ix, const void* queries, int64_t q0, int64_t cnt, 
     const int64_t cap = rank_prefix_cap(nsel, ix->nlist);
     chunk_prefix = cnt < (1 << 18) ? cnt : (1 << 18);
     int st;
-    if ((st = ensure(ix->cand, (size_t)chunk_prefix * cap * sizeof(unsigned long long))) ||
-        (st = ensure(ix->ccount, (size_t)chunk_prefix * sizeof(int32_t))))
+    if ((st = ensure(ix, ix->cand, (size_t)chunk_prefix * cap * sizeof(unsigned long long))) ||
+        (st = ensure(ix, ix->ccount, (size_t)chunk_prefix * sizeof(int32_t))))
       return st;
   }
   return rank_queries_in(ix, queries, q0, cnt, nsel, ldp, pl, P, rc,
@@ -447,6 +481,11 @@ ScanArgs make_scan_args(sieve_index* ix, const void* queries, const int64_t* exc
   a.tile_q = pl.tile_q;
   a.wide = pl.wide ? 1 : 0;
   a.tau = pl.tau;
+  a.dtype = ix->dtype;
+  if (pl.screen) {
+    a.v8 = ix->v8;
+    a.q8 = ix->q8.p;
+  }
   return a;
 }
 
@@ -457,9 +496,13 @@ int run_round(sieve_index* ix, const ScanArgs& sa, int n_items, int64_t q0, cons
               const SearchPlan& pl, hipStream_t s, bool timed, int* at) {
   RoundCounters* rc = (RoundCounters*)ix->rc.p;
   const bool dense = (int64_t)n_items >= (int64_t)pl.dense_q * ix->nlist;
-  const int chunk = dense ? pl.row_chunk_dense : pl.row_chunk;
+  int chunk = dense ? pl.row_chunk_dense : pl.row_chunk;
   int group = pl.group_q, tile_q = pl.tile_q, grid = pl.scan_grid;
-  if (pl.rega) {
+  if (pl.screen) {
+    chunk = dense ? pl.s_chunk_dense : pl.s_chunk;
+    group = tile_q = screen_tile_q(ix->d, dense);
+    grid = ((ix->cus * screen_grid_per_cu(ix->d) + 7) / 8) * 8;
+  } else if (pl.rega) {
     // dense rounds: 128-query tiles of whole lists, one work-group per CU;
     // sparse rounds: 64-query tiles of 512 rows, two per CU
     // (SIEVE_REGA_DENSE = 0 gives dense rounds the sparse shape; tuning only)
@@ -477,7 +520,9 @@ int run_round(sieve_index* ix, const ScanArgs& sa, int n_items, int64_t q0, cons
                                (int32_t*)ix->tile_off.p, rc, fuse ? (Tile*)ix->tiles.p : nullptr,
                                tile_cap, s));
   HIP_TRY(launch_sched_scatter((const Item*)ix->items.p, n_items, P, pl.n, (int32_t)q0, sa.exclude,
-                               (int32_t*)ix->cursor.p, (BItem*)ix->bucket.p, s));
+                               (int32_t*)ix->cursor.p, (BItem*)ix->bucket.p,
+                               pl.screen ? (const ScreenParam*)ix->qpar.p : nullptr,
+                               pl.screen ? ix->lpar : nullptr, pl.tau, ix->d, s));
   if (!fuse)
     HIP_TRY(launch_sched_tiles((int32_t*)ix->cnt.p, (const int32_t*)ix->item_off.p,
                                (const int32_t*)ix->tile_off.p, ix->offsets, ix->nlist, chunk,
@@ -486,7 +531,10 @@ int run_round(sieve_index* ix, const ScanArgs& sa, int n_items, int64_t q0, cons
   ScanArgs sr = sa;
   sr.dynamic = scan_dynamic(ix, n_items, dense, chunk, group, grid);
   sr.tile_q = tile_q;
-  HIP_TRY(launch_scan(ix->dtype, sr, grid, s));
+  if (pl.screen)
+    HIP_TRY(launch_screen_scan(sr, grid, s));
+  else
+    HIP_TRY(launch_scan(ix->dtype, sr, grid, s));
   const int e2 = mark(ix, timed, s);
   span(ix, kSched, e0, e1);
   span(ix, kScan, e1, e2);
@@ -569,6 +617,7 @@ int search_impl(sieve_index* ix, const void* queries, int64_t nq, const int64_t*
 
   int pool_retries = 0;
   for (;;) {
+    if (!ix->v8) pl.screen = false;  // given back by a workspace that grew
     reset_timeline(ix);
     int rounds = 0;
     int64_t items_total = 0;
@@ -596,8 +645,12 @@ int search_impl(sieve_index* ix, const void* queries, int64_t nq, const int64_t*
       if (pl.mode != 2) f.seg[5] = {(int32_t*)ix->have.p, nq, pl.r0};
       HIP_TRY(launch_fill_multi(f, s));
     }
+    if (pl.screen)
+      HIP_TRY(launch_screen_queries(ix->dtype, ix->d, queries, nq, ix->q8.p,
+                                    (ScreenParam*)ix->qpar.p, s));
+    unsigned long long scr_seen = 0, rows_seen = 0;  // the screen's counters so far
     bool spec_used = false;  // a round kept the rank bitmap (its ranks may pass stop lines)
-    RoundSummary sm = {0, 0, 0, 0, 0, 0, 0};  // the host's view of the last round
+    RoundSummary sm = {};  // the host's view of the last round
     int32_t* P = (int32_t*)ix->P.p;
 
     if (pl.mode != 2) {
@@ -612,6 +665,7 @@ int search_impl(sieve_index* ix, const void* queries, int64_t nq, const int64_t*
       span(ix, kRank, r0, at);
       int64_t n_items = nq * s0;
       while (n_items > 0) {
+        if (!ix->v8) pl.screen = false;
         // speculative issue from round spec_round on: its scans keep the rank bitmap
         const bool spec_now = pl.spec && rounds >= pl.spec_round;
         if (spec_now && !spec_used) {
@@ -644,6 +698,15 @@ int search_impl(sieve_index* ix, const void* queries, int64_t nq, const int64_t*
         sm.rank_error = rs->rank_error;
         sm.heavy = rs->heavy;
         sm.hits = rs->hits;
+        if (pl.screen) {
+          // the screen pays while few pairs pass it: a pair scored exactly
+          // costs about 16 pairs of the exact scan's tiles (one pair of a
+          // 16 x 16 product block is used)
+          const unsigned long long scr = rs->screened, rows = rs->item_rows;
+          if ((scr - scr_seen) * kScreenPassInv > rows - rows_seen) pl.screen = false;
+          scr_seen = scr;
+          rows_seen = rows;
+        }
         if (rs->sched_error)
           return fail(SIEVE_EINTERNAL, "a round's tiles exceeded the tile buffer");
         items_total += n_items;
@@ -653,8 +716,8 @@ int search_impl(sieve_index* ix, const void* queries, int64_t nq, const int64_t*
           // stop lines passed the ordered prefix: order every rank of those queries
           const int x0 = at;
           const int64_t rb = (int64_t)ix->d * e;
-          if ((st = ensure(ix->qext, (size_t)n_ext * rb)) ||
-              (st = ensure(ix->Pext, (size_t)n_ext * pl.n * sizeof(int32_t))))
+          if ((st = ensure(ix, ix->qext, (size_t)n_ext * rb)) ||
+              (st = ensure(ix, ix->Pext, (size_t)n_ext * pl.n * sizeof(int32_t))))
             return st;
           HIP_TRY(launch_gather_rows(ext, n_ext, queries, rb, ix->qext.p, s));
           if ((st = rank_queries(ix, ix->qext.p, 0, n_ext, pl.n, pl.n, pl, (int32_t*)ix->Pext.p,
@@ -688,6 +751,7 @@ int search_impl(sieve_index* ix, const void* queries, int64_t nq, const int64_t*
                                     s));
         at = mark(ix, timed, s);
         span(ix, kRank, r0, at);
+        if (!ix->v8) pl.screen = false;
         if ((st = run_round(ix, sa, (int)(c * pl.n), q0, P, pl, s, timed, &at))) return st;
         items_total += c * pl.n;
         ++rounds;
@@ -722,7 +786,7 @@ int search_impl(sieve_index* ix, const void* queries, int64_t nq, const int64_t*
     const int64_t n_heavy = sm.heavy;
     if (n_heavy > ix->heavy_cap) {
       ix->heavy_cap = n_heavy + n_heavy / 4 + 1024;
-      if ((st = ensure(ix->heavy, (size_t)ix->heavy_cap * sizeof(HeavyRec)))) return st;
+      if ((st = ensure(ix, ix->heavy, (size_t)ix->heavy_cap * sizeof(HeavyRec)))) return st;
       if (++pool_retries > 4) return fail(SIEVE_EINTERNAL, "overflow records kept overflowing");
       continue;
     }
@@ -760,8 +824,8 @@ int search_impl(sieve_index* ix, const void* queries, int64_t nq, const int64_t*
     if (hits > ix->pool_cap) {
       // the pool overflowed: grow it and run again (the search is deterministic)
       ix->pool_cap = hits + hits / 8 + 4096;
-      if ((st = ensure(ix->pool, (size_t)ix->pool_cap * sizeof(Hit)))) return st;
-      if ((st = ensure(ix->pool_sorted, (size_t)ix->pool_cap * sizeof(Hit)))) return st;
+      if ((st = ensure(ix, ix->pool, (size_t)ix->pool_cap * sizeof(Hit)))) return st;
+      if ((st = ensure(ix, ix->pool_sorted, (size_t)ix->pool_cap * sizeof(Hit)))) return st;
       if (++pool_retries > 4) return fail(SIEVE_EINTERNAL, "candidate pool kept overflowing");
       continue;
     }
@@ -865,6 +929,32 @@ int plan_search(const sieve_index* ix, int64_t nq, int32_t k, float tau, int32_t
       scan_uses_rega(ix->dtype, ix->d) ? whole : (avg_len <= 2048 ? 4096 : 1024));
   if (pl->row_chunk_dense < pl->row_chunk) pl->row_chunk_dense = pl->row_chunk;
   pl->dense_q = env_int("SIEVE_DENSE_Q", 64);
+  // Screened scans: where few pairs can pass, by the share of sampled row
+  // pairs of one list whose score is within the slack of tau or above (a
+  // query's first lists are the likes of its own).  The first round is checked
+  // against the same limit as it runs.  SIEVE_SCREEN = 0 turns them off, 2
+  // forces them where the copy exists (tests).
+  const int scr = env_count("SIEVE_SCREEN", 1);
+  pl->screen = ix->v8 && scr != 0 && arena_on(ix);
+  if (pl->screen && scr != 2) {
+    const auto& v = ix->scr_scores;
+    const float lim = (float)((double)tau - ix->scr_slack);
+    const size_t pass = (size_t)(v.end() - std::lower_bound(v.begin(), v.end(), lim));
+    if (v.empty() || pass * kScreenPassInv > v.size()) pl->screen = false;
+  }
+  {
+    // register-held queries take whole lists in dense rounds, like the exact
+    // kernels; tiles that stage long rows in LDS 4,096 rows
+    const bool reg = ix->d <= 128;
+    const int64_t lim = ((int64_t)INT32_MAX / (64 * std::max(screen_chunks(ix->d), 1))) / 64 * 64;
+    auto rows = [&](const char* knob, int64_t dflt) {
+      const int64_t r = (env_int(knob, (int)dflt) + 63ll) / 64 * 64;
+      return (int)std::max<int64_t>(64, std::min(r, lim));
+    };
+    pl->s_chunk = rows("SIEVE_SCREEN_CHUNK", reg ? 2048 : 1024);
+    pl->s_chunk_dense = std::max(pl->s_chunk, rows("SIEVE_SCREEN_CHUNK_DENSE", reg ? whole : 4096));
+    if (pl->screen) pl->min_group = std::min(pl->min_group, screen_tile_q(ix->d, false));
+  }
   // Speculative issue needs the rank packed beside the query in pool entries
   // (queries < 2^kRankShift) and a stop rule that can stop early (W < n).
   pl->spec = speculative && mode == 0 && W < pl->n && nq <= (int64_t)kQueryMask + 1;
@@ -1005,9 +1095,6 @@ SIEVE_API int sieve_load_index(const void* vectors, int32_t dtype, int64_t n, in
   std::vector<int64_t> hfoff(nlist + 1, 0);
   for (int l = 0; l < nlist; ++l) hfoff[l + 1] = hfoff[l] + (off[l + 1] - off[l] + 15) / 16 * 16;
   const size_t vfbytes = vector_frag_bytes(dtype, d, hfoff[nlist]);
-  // the partition starts are read for every tile of a compile-time dimension,
-  // also when the store is empty (then no row is)
-  const bool vfixed = vector_frag_bytes(dtype, d, 16) > 0;
   hipError_t err;
   if ((err = hipMalloc(&ix->vectors, vbytes ? vbytes : 16)) != hipSuccess ||
       (err = hipMalloc((void**)&ix->offsets, sizeof(int64_t) * (nlist + 1))) != hipSuccess ||
@@ -1015,7 +1102,7 @@ SIEVE_API int sieve_load_index(const void* vectors, int32_t dtype, int64_t n, in
       (err = hipMalloc(&ix->centroids, cbytes)) != hipSuccess ||
       (fbytes && (err = hipMalloc(&ix->cfrag, fbytes)) != hipSuccess) ||
       (vfbytes && (err = hipMalloc(&ix->vfrag, vfbytes)) != hipSuccess) ||
-      (vfixed && (err = hipMalloc((void**)&ix->foff, sizeof(int64_t) * (nlist + 1))) != hipSuccess)) {
+      (err = hipMalloc((void**)&ix->foff, sizeof(int64_t) * (nlist + 1))) != hipSuccess) {
     (void)hipGetLastError();
     return bail(fail(SIEVE_ENOMEM, "index allocation failed: %s", hipGetErrorString(err)));
   }
@@ -1024,10 +1111,37 @@ SIEVE_API int sieve_load_index(const void* vectors, int32_t dtype, int64_t n, in
       (n > 0 && (err = hipMemcpyAsync(ix->ids, ids, sizeof(int64_t) * n, hipMemcpyDeviceToDevice, s)) != hipSuccess) ||
       (err = hipMemcpyAsync(ix->centroids, centroids, cbytes, hipMemcpyDeviceToDevice, s)) != hipSuccess ||
       (fbytes && (err = launch_centroid_frag(dtype, d, ix->centroids, nlist, ix->cfrag, s)) != hipSuccess) ||
-      (vfixed && (err = hipMemcpyAsync(ix->foff, hfoff.data(), sizeof(int64_t) * (nlist + 1),
-                                        hipMemcpyHostToDevice, s)) != hipSuccess) ||
-      (vfbytes && (err = launch_vector_frag(dtype, d, ix->vectors, ix->offsets, ix->foff, nlist,
-                                            hfoff[nlist], ix->vfrag, s)) != hipSuccess))
+      (err = hipMemcpyAsync(ix->foff, hfoff.data(), sizeof(int64_t) * (nlist + 1),
+                            hipMemcpyHostToDevice, s)) != hipSuccess)
+    return bail(fail(SIEVE_EDEVICE, "index copy failed: %s", hipGetErrorString(err)));
+  // The 8-bit copy of the screened scan is taken where it fits well (at most a
+  // third of what is free now); without it every scan is exact.
+  std::vector<ScreenParam> hl;
+  std::vector<float> hs;
+  if (screen_chunks(d) > 0 && n > 0) {
+    const size_t sbytes = screen_rows_bytes(d, hfoff[nlist]);
+    size_t mfree = 0, mtotal = 0;
+    if (hipMemGetInfo(&mfree, &mtotal) == hipSuccess && sbytes <= mfree / 3 &&
+        hipMalloc((void**)&ix->lpar, sizeof(ScreenParam) * nlist) == hipSuccess &&
+        ensure(ix, ix->scores, (size_t)kScreenSample * 256 * sizeof(float)) == SIEVE_OK &&
+        hipMalloc(&ix->v8, sbytes) == hipSuccess) {
+      hl.resize(nlist);
+      hs.resize((size_t)kScreenSample * 256);
+    } else {
+      (void)hipGetLastError();
+      if (ix->v8) (void)hipFree(ix->v8);
+      ix->v8 = nullptr;
+    }
+  }
+  if ((err = launch_index_rows(dtype, d, ix->vectors, ix->offsets, ix->foff, nlist, hfoff[nlist],
+                               ix->vfrag, ix->v8, ix->lpar, s)) != hipSuccess ||
+      (ix->v8 &&
+       ((err = launch_screen_sample(d, ix->v8, ix->offsets, ix->foff, nlist, ix->lpar,
+                                    (float*)ix->scores.p, s)) != hipSuccess ||
+        (err = hipMemcpyAsync(hl.data(), ix->lpar, sizeof(ScreenParam) * nlist,
+                              hipMemcpyDeviceToHost, s)) != hipSuccess ||
+        (err = hipMemcpyAsync(hs.data(), ix->scores.p, hs.size() * sizeof(float),
+                              hipMemcpyDeviceToHost, s)) != hipSuccess)))
     return bail(fail(SIEVE_EDEVICE, "index copy failed: %s", hipGetErrorString(err)));
   std::vector<uint8_t> hc(cbytes);
   if ((err = hipMemcpyAsync(hc.data(), centroids, cbytes, hipMemcpyDeviceToHost, s)) != hipSuccess ||
@@ -1043,6 +1157,22 @@ SIEVE_API int sieve_load_index(const void* vectors, int32_t dtype, int64_t n, in
     if (ss > cmax) cmax = ss;
   }
   ix->cmax = sqrt(cmax) * (1.0 + 1e-12);
+  if (ix->v8) {
+    double err = 0.0, norm = 0.0;
+    int64_t lists = 0;
+    for (const ScreenParam& p : hl)
+      if (p.norm > 0.f && isfinite(p.norm) && isfinite(p.err)) {
+        err += p.err;
+        norm += p.norm;
+        ++lists;
+      }
+    if (lists > 0) {
+      ix->scr_slack = 2.0 * (err / (double)lists) * (norm / (double)lists);
+      for (float x : hs)
+        if (x > -INFINITY) ix->scr_scores.push_back(x);  // (NaN left out)
+      std::sort(ix->scr_scores.begin(), ix->scr_scores.end());
+    }
+  }
   if (!isfinite(ix->cmax)) return bail(fail(SIEVE_EINVAL, "centroids contain inf or NaN"));
   *out = ix;
   return SIEVE_OK;
@@ -1061,6 +1191,8 @@ SIEVE_API void sieve_free_index(sieve_index* ix) {
   if (ix->cfrag) (void)hipFree(ix->cfrag);
   if (ix->vfrag) (void)hipFree(ix->vfrag);
   if (ix->foff) (void)hipFree(ix->foff);
+  if (ix->v8) (void)hipFree(ix->v8);
+  if (ix->lpar) (void)hipFree(ix->lpar);
   if (ix->rc_host) (void)hipHostFree(ix->rc_host);
   if (ix->rs_host) (void)hipHostFree(ix->rs_host);
   for (hipEvent_t e : ix->ev_pool) (void)hipEventDestroy(e);
@@ -1084,7 +1216,10 @@ SIEVE_API int sieve_search(const sieve_index* idx, const void* queries, int64_t 
   if ((st = plan_search(ix, nq, k, tau, W, nprobe_max, lookahead_mode(lookahead),
                         lookahead == SIEVE_LOOKAHEAD_SPECULATIVE, &pl)))
     return st;
-  if (lookahead == SIEVE_LOOKAHEAD_SERIAL) pl.group_q = 1;  // no query shares a partition scan
+  if (lookahead == SIEVE_LOOKAHEAD_SERIAL) {  // no query shares a partition scan
+    pl.group_q = 1;
+    pl.screen = false;
+  }
   if (stats) memset(stats, 0, sizeof(*stats));
   if (nq == 0) {
     if (stats) stats->nprobe_eff = pl.n;
@@ -1126,8 +1261,8 @@ SIEVE_API int sieve_rank(const sieve_index* idx, const void* queries, int64_t nq
   HIP_TRY(hipGetDevice(&dev));
   if (dev != ix->device) return fail(SIEVE_EINVAL, "current device differs from the index's");
   hipStream_t s = (hipStream_t)stream;
-  if ((st = ensure(ix->scores, (size_t)pl.rank_chunk * ix->nlist * sizeof(float)))) return st;
-  if ((st = ensure(ix->rc, sizeof(RoundCounters)))) return st;
+  if ((st = ensure(ix, ix->scores, (size_t)pl.rank_chunk * ix->nlist * sizeof(float)))) return st;
+  if ((st = ensure(ix, ix->rc, sizeof(RoundCounters)))) return st;
   if (!ix->rc_host) HIP_TRY(hipHostMalloc((void**)&ix->rc_host, sizeof(RoundCounters), 0));
   RoundCounters* rc = (RoundCounters*)ix->rc.p;
   const int div0 = pl.rank_div;
@@ -1315,9 +1450,9 @@ int calibrated_impl(sieve_index* ix, const void* queries, int64_t nq, const int6
       if (!seen[(size_t)q]) rows[(size_t)j++] = (int32_t)q;
   }
   const int64_t gather_rows = ns > 0 ? std::max(ns, nr) : 0;
-  if ((st = ensure(ix->cal_idx, (size_t)nq * 4)) ||
-      (st = ensure(ix->cal_q, (size_t)gather_rows * row_bytes)) ||
-      (exclude_ids && (st = ensure(ix->cal_x, (size_t)gather_rows * 8))))
+  if ((st = ensure(ix, ix->cal_idx, (size_t)nq * 4)) ||
+      (st = ensure(ix, ix->cal_q, (size_t)gather_rows * row_bytes)) ||
+      (exclude_ids && (st = ensure(ix, ix->cal_x, (size_t)gather_rows * 8))))
     return st;
   if (ns > 0)
     HIP_TRY(hipMemcpyAsync(ix->cal_idx.p, rows.data(), (size_t)nq * 4, hipMemcpyHostToDevice, s));
@@ -1330,9 +1465,9 @@ int calibrated_impl(sieve_index* ix, const void* queries, int64_t nq, const int6
   sieve_stats part;
   if (ns > 0) {
     const int32_t words = (pf.n + 31) / 32;
-    if ((st = ensure(ix->cal_bits, (size_t)ns * words * 4)) ||
-        (st = ensure(ix->cal_rank, (size_t)ns * k * 4)) ||
-        (st = ensure(ix->cal_hist, (size_t)(pf.n + 3) * 8)))
+    if ((st = ensure(ix, ix->cal_bits, (size_t)ns * words * 4)) ||
+        (st = ensure(ix, ix->cal_rank, (size_t)ns * k * 4)) ||
+        (st = ensure(ix, ix->cal_hist, (size_t)(pf.n + 3) * 8)))
       return st;
     HIP_TRY(launch_gather_rows(d_rows, (int32_t)ns, queries, row_bytes, gq, s));
     if (gx) HIP_TRY(launch_gather_i64(d_rows, ns, exclude_ids, gx, s));
@@ -1428,7 +1563,10 @@ SIEVE_API int sieve_search_multi(const sieve_index* const* idxs, int32_t nidx,
     if ((st = plan_search(ix, nq, k, tau, W, nprobe_max, lookahead_mode(lookahead),
                           lookahead == SIEVE_LOOKAHEAD_SPECULATIVE, &plans[i])))
       return st;
-    if (lookahead == SIEVE_LOOKAHEAD_SERIAL) plans[i].group_q = 1;
+    if (lookahead == SIEVE_LOOKAHEAD_SERIAL) {
+      plans[i].group_q = 1;
+      plans[i].screen = false;
+    }
   }
   if (stats) memset(stats, 0, sizeof(*stats));
   if (nq == 0) return SIEVE_OK;
@@ -1436,9 +1574,9 @@ SIEVE_API int sieve_search_multi(const sieve_index* const* idxs, int32_t nidx,
   // per-index results, [nidx][nq][k], in the first index's workspace
   sieve_index* ws = const_cast<sieve_index*>(idxs[0]);
   const size_t rows = (size_t)nidx * (size_t)nq;
-  if ((st = ensure(ws->mix_ids, rows * k * sizeof(int64_t))) ||
-      (st = ensure(ws->mix_scores, rows * k * sizeof(float))) ||
-      (st = ensure(ws->mix_probes, rows * sizeof(int32_t))))
+  if ((st = ensure(ws, ws->mix_ids, rows * k * sizeof(int64_t))) ||
+      (st = ensure(ws, ws->mix_scores, rows * k * sizeof(float))) ||
+      (st = ensure(ws, ws->mix_probes, rows * sizeof(int32_t))))
     return st;
   int64_t* mids = (int64_t*)ws->mix_ids.p;
   float* msc = (float*)ws->mix_scores.p;
@@ -1493,9 +1631,9 @@ SIEVE_API int sieve_search_multi_calibrated(const sieve_index* const* idxs, int3
   // per-index results, [nidx][nq][k], in the first index's workspace
   sieve_index* ws = const_cast<sieve_index*>(idxs[0]);
   const size_t rows = (size_t)nidx * (size_t)nq;
-  if ((st = ensure(ws->mix_ids, rows * k * sizeof(int64_t))) ||
-      (st = ensure(ws->mix_scores, rows * k * sizeof(float))) ||
-      (st = ensure(ws->mix_probes, rows * sizeof(int32_t))))
+  if ((st = ensure(ws, ws->mix_ids, rows * k * sizeof(int64_t))) ||
+      (st = ensure(ws, ws->mix_scores, rows * k * sizeof(float))) ||
+      (st = ensure(ws, ws->mix_probes, rows * sizeof(int32_t))))
     return st;
   int64_t* mids = (int64_t*)ws->mix_ids.p;
   float* msc = (float*)ws->mix_scores.p;

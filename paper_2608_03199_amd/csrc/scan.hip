@@ -30,7 +30,7 @@
 // (see the kernel); every block exits after its claims run dry, at most
 // tiles + 8 claims per block.
 #include "mfma_tile.h"
-#include "wave_sort.h"
+#include "tile_end.h"
 
 namespace sieve {
 namespace {
@@ -96,20 +96,6 @@ constexpr int rega_max_qb() {
   return kOcc == 1 ? kRegAQB : 4;
 }
 
-// Unsigned key whose order is the float order of finite and infinite scores
-// (sign flipped for positive values, all bits flipped for negative ones; -0
-// takes +0's key, as the two compare equal).
-__device__ __forceinline__ uint32_t order_key(float x) {
-  const uint32_t u = __float_as_uint(x == 0.0f ? 0.0f : x);
-  return (u & 0x80000000u) ? ~u : (u | 0x80000000u);
-}
-
-// Top-k selection at the end of a tile: score keys per lane held in
-// registers, and the LDS arena entries (8 bytes) each wave borrows to compact
-// 64 segment positions.
-constexpr int kSelR = 8;
-constexpr int kSelSlots = 64 * (int)sizeof(int32_t) / (int)sizeof(TileSpill);
-
 // Largest of one query block's four accumulator elements (the same tree in
 // the vote and in the candidate test, so the two share it).
 __device__ __forceinline__ float block_max(const f32x4& v) {
@@ -145,16 +131,7 @@ __global__ __launch_bounds__(kNT, kOcc) void scan_kernel(ScanArgs a) {
   __shared__ int32_t s_q[2][kTQ];     // item sets: the running tile and the next
   __shared__ int32_t s_rank[2][kTQ];
   __shared__ int64_t s_ex[2][kTQ];
-  __shared__ int32_t s_hits[kTQ];  // qualifying rows per staged query in this tile
-  __shared__ int32_t s_over[kTQ];  // staged queries whose candidates overflowed
-  __shared__ int32_t s_lost[kTQ];  // their qualifying rows the full arena did not take
-  __shared__ int32_t s_sel[kTQ];   // staged queries selected from slots + spill
-  __shared__ int32_t s_soff[kTQ];  // their segment in the sorted spill
-  __shared__ int32_t s_scur[kTQ];
-  __shared__ int32_t s_poff[kTQ];  // their first pool entry (after the tile's base)
-  __shared__ int32_t s_pool_n, s_over_n, s_sel_n, s_rbase;
-  __shared__ int32_t s_wcnt[kNT / 64];  // pairs each wave appended in this tile
-  __shared__ unsigned long long s_pbase;
+  __shared__ TileShared<kTQ, kNT> S;
   // per work-group: the arena's global extension (spill_cap entries), then
   // the tile's whole arena grouped by query (LDS part and extension)
   TileSpill* const arena_g = a.spill + (size_t)blockIdx.x * arena_block_entries(a.spill_cap);
@@ -248,13 +225,13 @@ __global__ __launch_bounds__(kNT, kOcc) void scan_kernel(ScanArgs a) {
     s_first[1] = kShallow ? -1 : claim();
     s_first[2] = kShallow ? -1 : claim();
     s_first[3] = kShallow ? -1 : claim();
-    s_pool_n = 0;
-    s_over_n = 0;
-    s_sel_n = 0;
+    S.pool_n = 0;
+    S.over_n = 0;
+    S.sel_n = 0;
   }
   if (threadIdx.x < kTQ) {
-    s_hits[threadIdx.x] = 0;
-    s_lost[threadIdx.x] = 0;
+    S.hits[threadIdx.x] = 0;
+    S.lost[threadIdx.x] = 0;
   }
   __syncthreads();
   int t = s_first[0], tn = s_first[1], ta = s_first[2], tb = s_first[3];
@@ -383,7 +360,7 @@ __global__ __launch_bounds__(kNT, kOcc) void scan_kernel(ScanArgs a) {
         else if (pos - wcap < gcap)
           arena_g[wv * gcap + pos - wcap] = ent;
         else if (a.ids[row] != sex[i])
-          atomicAdd(&s_lost[i], 1);
+          atomicAdd(&S.lost[i], 1);
         ++pos;
       }
       __builtin_amdgcn_s_waitcnt(0);
@@ -462,7 +439,10 @@ __global__ __launch_bounds__(kNT, kOcc) void scan_kernel(ScanArgs a) {
           buf, g, (const char*)(D > 0 ? a.vfrag : a.vectors), row_bytes, r0, r1, qb_n, epi, fd);
       if constexpr (kShallow) put_items(nset, recN, itN);  // staged at the next tile's start
     }
-    if (lane == 0) s_wcnt[wv] = wcnt;
+    if (lane == 0) {
+      S.wcnt[wv] = min(wcnt, wcap);
+      S.gcnt[wv] = min(max(wcnt - wcap, 0), gcap);
+    }
     wcnt = 0;
     // this wave's staging copies and arena stores are complete (in L2)
     __builtin_amdgcn_s_waitcnt(0);
@@ -470,290 +450,18 @@ __global__ __launch_bounds__(kNT, kOcc) void scan_kernel(ScanArgs a) {
     if constexpr (kShallow && kMode == kStageRegA) {
       if (tn >= 0) dma_stage<DT>(lds, g, qbase, row_bytes, s_q[nset], recN.nq);
     }
-    // the arena's parts: pairs held per wave, their prefix; any global part?
-    int wn[kNT / 64], wpre[kNT / 64 + 1];
-    bool ext = false;
-    wpre[0] = 0;
-#pragma unroll
-    for (int w = 0; w < kNT / 64; ++w) {
-      const int cw = w < nwv ? s_wcnt[w] : 0;
-      wn[w] = min(cw, wcap + gcap);
-      ext |= cw > wcap;
-      wpre[w + 1] = wpre[w] + wn[w];
-    }
-    // Candidates in the arena's global extension were stored by other waves of
-    // the work-group: an acquire at agent scope invalidates the CU's vector L1,
-    // whose lines of that area may be stale (read in an earlier tile).
-    if (ext) __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
-
-    // End of the tile.  The arena's pairs are counted per staged query, each
-    // query's own row excluded (a pair whose row id is the query's excluded
-    // id); four pairs per thread are in flight at once.
-    const int na = wpre[kNT / 64];  // pairs the arena holds
-    auto arena_at = [&](int e) -> TileSpill {
-      int w = 0;
-#pragma unroll
-      for (int u = 1; u < kNT / 64; ++u) w += e >= wpre[u] ? 1 : 0;
-      const int ew = e - wpre[w];
-      return ew < wcap ? s_arena[w * wcap + ew] : arena_g[w * gcap + ew - wcap];
-    };
-    auto excluded = [&](const TileSpill& ts, int64_t id) {
-      return id == sex[ts.rowq >> kSpillRowBits];
-    };
-    auto row_id = [&](const TileSpill& ts) -> int64_t {
-      return a.ids[r0 + (ts.rowq & ((1u << kSpillRowBits) - 1u))];
-    };
-    for (int e0 = threadIdx.x; e0 < na; e0 += 4 * (int)blockDim.x) {
-      TileSpill ts[4];
-      int64_t id[4];
-#pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        const int e = e0 + u * (int)blockDim.x;
-        ts[u] = arena_at(e < na ? e : e0);
-        id[u] = row_id(ts[u]);
-      }
-#pragma unroll
-      for (int u = 0; u < 4; ++u)
-        if (e0 + u * (int)blockDim.x < na && !excluded(ts[u], id[u]))
-          atomicAdd(&s_hits[ts[u].rowq >> kSpillRowBits], 1);
-    }
-    __syncthreads();
-
-    // Per staged query: the hit flag; then its candidates to the pool (all of
-    // them, or its exact top k when it has more), or, when the arena could not
-    // take all of them, a heavy record for the exact top-k pass.
-    int c = 0, keep = 0;
-    if ((int)threadIdx.x < nq) {
-      const int lost = s_lost[threadIdx.x];
-      c = s_hits[threadIdx.x];
-      if (c + lost > 0) {
-        const int q = sq[threadIdx.x];
-        const int rk = srank[threadIdx.x];
-        atomicMax(&a.lmax[q], rk + 1);
-        if (a.hitbits)
-          atomicOr(&a.hitbits[(int64_t)q * a.hit_words + (rk >> 5)], 1u << (rk & 31));
-        if (lost == 0) {
-          keep = min(c, a.k);
-          s_poff[threadIdx.x] = atomicAdd(&s_pool_n, keep);
-          atomicAdd(&a.hcount[q], keep);
-          if (c > a.k) s_sel[atomicAdd(&s_sel_n, 1)] = threadIdx.x;
-        } else {
-          s_over[atomicAdd(&s_over_n, 1)] = threadIdx.x;
-        }
-      }
-      c += lost;
-    }
-    {
-      // qualifying pairs of the tile, for the statistics: one add per wave
-      unsigned long long cs = (unsigned long long)c;
-      for (int o = 32; o > 0; o >>= 1) cs += __shfl_xor(cs, o);
-      if (lane == 0 && cs) atomicAdd(&a.rc->cands, cs);
-    }
-    __syncthreads();
-    const int pool_n = s_pool_n, over_n = s_over_n, sel_n = s_sel_n;  // block-uniform
-    if (pool_n + over_n > 0) {
-      if (threadIdx.x == 0) {
-        s_pbase = pool_n ? atomicAdd(a.pool_count, (unsigned long long)pool_n) : 0ull;
-        s_rbase = over_n ? atomicAdd(&a.rc->heavy, (over_n + kHeavyQ - 1) / kHeavyQ) : 0;
-      }
-      if ((int)threadIdx.x < nq) s_scur[threadIdx.x] = 0;
-      // segments of the sorted area, for the queries with more than k pairs
-      // only (wave 0: an exclusive prefix over s_sel, kPer consecutive
-      // entries per lane)
-      if (sel_n > 0 && threadIdx.x < 64) {
-        constexpr int kPer = (kTQ + 63) / 64;
-        int v[kPer];
-        int tot = 0;
-#pragma unroll
-        for (int u = 0; u < kPer; ++u) {
-          const int j = kPer * lane + u;
-          v[u] = j < sel_n ? s_hits[s_sel[j]] : 0;
-          tot += v[u];
-        }
-        int inc = tot;
-#pragma unroll
-        for (int o = 1; o < 64; o <<= 1) {
-          const int t = __shfl_up(inc, o);
-          if (lane >= o) inc += t;
-        }
-        int ex = inc - tot;
-#pragma unroll
-        for (int u = 0; u < kPer; ++u) {
-          const int j = kPer * lane + u;
-          if (j < sel_n) s_soff[s_sel[j]] = ex;
-          ex += v[u];
-        }
-      }
-      __syncthreads();
-      if ((int)threadIdx.x < over_n) {
-        const int gi = threadIdx.x / kHeavyQ, m = threadIdx.x % kHeavyQ;
-        const int64_t rec = (int64_t)s_rbase + gi;
-        if (rec < a.heavy_cap) {
-          HeavyRec* hr = a.heavy + rec;
-          const int i = s_over[threadIdx.x];
-          hr->q[m] = sq[i];
-          hr->rank[m] = srank[i];
-          hr->ex[m] = sex[i];
-          if (m == 0) {
-            hr->r0 = r0;
-            hr->fd = fd;
-            hr->nrows = (int32_t)(r1 - r0);
-            hr->nq = min(kHeavyQ, over_n - gi * kHeavyQ);
-          }
-        }
-      }
-      if (pool_n > 0) {
-        // The arena's pairs, own rows and heavy queries left out: a query
-        // with at most k of them writes them to its pool segment directly;
-        // one with more groups them in the sorted area (counting sort) for
-        // the exact top-k merge below.  Four pairs per thread in flight.
-        const int k = a.k;
-        for (int e0 = threadIdx.x; e0 < na; e0 += 4 * (int)blockDim.x) {
-          TileSpill ts[4];
-          int64_t id[4];
-#pragma unroll
-          for (int u = 0; u < 4; ++u) {
-            const int e = e0 + u * (int)blockDim.x;
-            ts[u] = arena_at(e < na ? e : e0);
-            id[u] = row_id(ts[u]);
-          }
-#pragma unroll
-          for (int u = 0; u < 4; ++u) {
-            const int qs = (int)(ts[u].rowq >> kSpillRowBits);
-            if (e0 + u * (int)blockDim.x >= na || id[u] == sex[qs] || s_lost[qs] > 0) continue;
-            const int ci = s_hits[qs];
-            const int slot = atomicAdd(&s_scur[qs], 1);
-            if (ci <= k) {
-              const unsigned long long pi = s_pbase + (unsigned long long)(s_poff[qs] + slot);
-              if ((int64_t)pi < a.pool_cap) {
-                Hit hv;
-                hv.score = ts[u].score;
-                hv.q = a.hitbits ? (sq[qs] | (srank[qs] << kRankShift)) : sq[qs];
-                hv.id = id[u];
-                a.pool[pi] = hv;
-              }
-            } else {
-              arena_srt[s_soff[qs] + slot] = SrtEnt{ts[u].score, 0, id[u]};
-            }
-          }
-        }
-        if (sel_n > 0) {
-          // the grouped area is read by other waves: stores complete,
-          // barrier, L1 invalidated (as above)
-          __builtin_amdgcn_s_waitcnt(0);
-          __syncthreads();
-          __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
-          // queries with more than k: one wave selects the query's top k from
-          // its segment.  Up to kSelR * 64 pairs: their score keys sit in
-          // registers, kSelR per lane; the k-th largest of the 64 lane maxima (a radix
-          // select over order-preserving score keys, ballots only) is a lower
-          // bound L on the k-th score, since k lanes hold a pair >= L.  When at
-          // most 64 pairs reach L, their positions are compacted through the
-          // wave's slice of the (now idle) LDS arena, and the pairs are loaded
-          // and sorted once: every pair of the top k is among them, ties at L
-          // included.  Otherwise (and for longer
-          // segments) the segment is merged 64 pairs at a time: the next batch
-          // loads under this one's sort, and a batch none of whose pairs
-          // reaches the k-th score kept so far is not sorted.
-          const Cand none = {-INFINITY, 0x7fffffffffffffffll, -1};
-          const bool slots_ok = arena_lds >= nwv * kSelSlots;  // uniform
-          int32_t* const wslot = (int32_t*)(s_arena + wv * kSelSlots);
-          for (int j = threadIdx.x >> 6; j < sel_n; j += blockDim.x >> 6) {
-            const int i = s_sel[j];
-            const int ci = s_hits[i];
-            const SrtEnt* seg = arena_srt + s_soff[i];
-            auto fetch = [&](int b0) -> Cand {
-              if (b0 + lane >= ci) return none;
-              const SrtEnt se = seg[b0 + lane];
-              return Cand{se.score, (long long)se.id, 0};
-            };
-            Cand top = none;
-            bool picked = false;
-            if (slots_ok && ci > 64 && ci <= kSelR * 64) {
-              uint32_t key[kSelR];
-              uint32_t kmax = 0;
-#pragma unroll
-              for (int r = 0; r < kSelR; ++r) {
-                const int e = r * 64 + lane;
-                key[r] = e < ci ? order_key(seg[e].score) : 0u;
-                kmax = max(kmax, key[r]);
-              }
-              // k-th largest lane maximum (every lane holds a pair: ci > 64)
-              uint32_t pre = 0, msk = 0;
-              int need = k;
-              for (int b = 31; b >= 0; --b) {
-                const uint32_t bit = 1u << b;
-                const int nhi = __popcll(__ballot((kmax & msk) == pre && (kmax & bit) != 0u));
-                if (nhi >= need)
-                  pre |= bit;
-                else
-                  need -= nhi;
-                msk |= bit;
-              }
-              int cnt = 0;
-#pragma unroll
-              for (int r = 0; r < kSelR; ++r) cnt += __popcll(__ballot(key[r] >= pre));
-              if (cnt <= 64) {
-                // segment positions of the pairs that reach L, then one load each
-                int pos = 0;
-#pragma unroll
-                for (int r = 0; r < kSelR; ++r) {
-                  const bool take = key[r] >= pre;
-                  const unsigned long long m = __ballot(take);
-                  if (take)
-                    wslot[pos + (int)__builtin_amdgcn_mbcnt_hi(
-                                    (uint32_t)(m >> 32),
-                                    __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u))] = r * 64 + lane;
-                  pos += __popcll(m);
-                }
-                __builtin_amdgcn_wave_barrier();
-                Cand c = none;
-                if (lane < cnt) {
-                  const SrtEnt se = seg[wslot[lane]];
-                  c = Cand{se.score, (long long)se.id, 0};
-                }
-                __builtin_amdgcn_wave_barrier();  // slots read before the next query's
-                top = wave_sort_desc<false>(c, lane);
-                picked = true;
-              }
-            }
-            if (!picked) {
-              top = wave_sort_desc<false>(fetch(0), lane);
-              Cand nxt = fetch(64);
-              for (int b0 = 64; b0 < ci; b0 += 64) {
-                Cand cnd = nxt;
-                nxt = fetch(b0 + 64);
-                const Cand kth = shfl_cand<false>(top, k - 1);
-                if (__ballot(!better(kth, cnd)) == 0ull) continue;
-                cnd = wave_sort_desc<false>(cnd, lane);
-                const Cand rv = shfl_cand<false>(cnd, 63 - lane);  // top ++ reverse(cnd): bitonic
-                top = better(top, rv) ? top : rv;
-                top = wave_merge_desc<false>(top, lane);
-              }
-            }
-            const int kk = min(ci, k);
-            const unsigned long long base = s_pbase + (unsigned long long)s_poff[i];
-            if (lane < kk && (int64_t)(base + lane) < a.pool_cap) {
-              Hit hv;
-              hv.score = top.s;
-              hv.q = a.hitbits ? (sq[i] | (srank[i] << kRankShift)) : sq[i];
-              hv.id = top.id;
-              a.pool[base + lane] = hv;
-            }
-          }
-        }
-      }
-    }
+    finish_tile<kTQ, kNT>(a, S, s_arena, arena_lds, wcap, arena_g, gcap, arena_srt, sq, srank, sex,
+                          nq, r0, r1, fd);
     __syncthreads();  // the counts and the spill are read; reset them for the next tile
     if ((int)threadIdx.x < nq) {
-      s_hits[threadIdx.x] = 0;
-      s_lost[threadIdx.x] = 0;
+      S.hits[threadIdx.x] = 0;
+      S.lost[threadIdx.x] = 0;
     }
     if (threadIdx.x == 0) {
       s_claim = t_claim;
-      s_pool_n = 0;
-      s_over_n = 0;
-      s_sel_n = 0;
+      S.pool_n = 0;
+      S.over_n = 0;
+      S.sel_n = 0;
     }
     if constexpr (kShallow) __builtin_amdgcn_s_waitcnt(0);  // the next tile's staging
     __syncthreads();
@@ -1096,61 +804,6 @@ int tile_rows(int dtype, int d) {
   int qb = (80 * 1024) / (16 * rb);
   qb = qb < 1 ? 1 : (qb > kQB ? kQB : qb);
   return 16 * qb;
-}
-
-namespace {
-// Fragment-order copy of the store (the layout FragStream reads): one thread
-// per 16-byte slot; slot (B nch + c) 64 + i + 16 s <- segment 4 c + s of copy
-// row p = 16 B + i, which is row off[L] + (p - foff[L]) of partition L
-// (foff[L] <= p < foff[L + 1]), or a padding row (zeros) past the
-// partition's last row; zeros past the row's segments too.
-__global__ __launch_bounds__(256) void vector_frag_kernel(
-    const char* __restrict__ vectors, const int64_t* __restrict__ off,
-    const int64_t* __restrict__ foff, int32_t nlist, int32_t row_bytes, int32_t nch,
-    u32x4* __restrict__ frag, int64_t nslots) {
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < nslots;
-       i += (int64_t)gridDim.x * blockDim.x) {
-    const int l = (int)(i & 63);
-    const int64_t bc = i >> 6;  // B nch + c
-    const int64_t blk = bc / nch;
-    const int c = (int)(bc - blk * nch);
-    const int64_t p = blk * 16 + (l & 15);
-    // partition of copy row p: the last L with foff[L] <= p
-    int lo = 0, hi = nlist;  // foff[lo] <= p < foff[hi]
-    while (hi - lo > 1) {
-      const int mid = (lo + hi) >> 1;
-      if (foff[mid] <= p) lo = mid; else hi = mid;
-    }
-    const int64_t k = p - foff[lo];
-    const int seg = 4 * c + (l >> 4);
-    u32x4 v = {0u, 0u, 0u, 0u};
-    if (k < off[lo + 1] - off[lo] && seg * 16 < row_bytes)
-      v = *(const u32x4*)(vectors + (off[lo] + k) * row_bytes + (int64_t)seg * 16);
-    frag[i] = v;
-  }
-}
-}  // namespace
-
-size_t vector_frag_bytes(int dtype, int d, int64_t frag_rows) {
-  const bool fixed = dtype == SIEVE_F32 ? (d == 64 || d == 128)
-                                        : (d == 64 || d == 128 || d == 768);
-  if (!fixed || frag_rows <= 0) return 0;
-  const int64_t row_bytes = (int64_t)d * (dtype == SIEVE_F32 ? 4 : 2);
-  return (size_t)((frag_rows + 15) / 16) * (size_t)((row_bytes + 63) / 64) * 1024;
-}
-
-hipError_t launch_vector_frag(int dtype, int d, const void* vectors, const int64_t* offsets,
-                              const int64_t* frag_offsets, int32_t nlist, int64_t frag_rows,
-                              void* frag, hipStream_t s) {
-  const size_t bytes = vector_frag_bytes(dtype, d, frag_rows);
-  if (bytes == 0 || nlist < 1) return hipSuccess;
-  const int32_t row_bytes = d * (dtype == SIEVE_F32 ? 4 : 2);
-  const int64_t nslots = (int64_t)(bytes / 16);
-  const int64_t blocks = (nslots + 255) / 256;
-  hipLaunchKernelGGL(vector_frag_kernel, dim3((unsigned)(blocks < (1 << 20) ? blocks : (1 << 20))),
-                     dim3(256), 0, s, (const char*)vectors, offsets, frag_offsets, nlist,
-                     row_bytes, (int32_t)((row_bytes + 63) / 64), (u32x4*)frag, nslots);
-  return hipGetLastError();
 }
 
 hipError_t launch_scan(int dtype, const ScanArgs& a, int32_t grid, hipStream_t s) {

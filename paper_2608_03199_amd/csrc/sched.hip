@@ -220,10 +220,29 @@ __global__ __launch_bounds__(kOffThreads) void sched_offsets_kernel(
   }
 }
 
+// The smallest 8-bit product of a (query, list) pair whose score may reach
+// tau (the bound is derived in screen_tile.h): floor((tau - slack) / (s_q s_l)),
+// held inside +-2^28, which no product of at most 1,024 dimensions leaves.  A
+// bound that is not a number, or norms whose product could overflow fp32 on
+// the way to a score, give -2^28 (every pair is scored).
+constexpr double kThrLim = 268435456.0;
+__device__ __forceinline__ int32_t screen_threshold(const ScreenParam& q, const ScreenParam& l,
+                                                    float tau, int32_t d) {
+  const double nq = (double)q.norm + (double)q.err;  // >= |q|
+  const double slack = (double)q.norm * l.err + (double)q.err * l.norm +
+                       2.0 * (double)(d + 2) * 5.9604644775390625e-08 * nq * l.norm;
+  const double t = ((double)tau - slack) / ((double)q.s * (double)l.s);
+  if (!(nq * l.norm < 1e37)) return -(int32_t)kThrLim;
+  if (!(t > -kThrLim)) return -(int32_t)kThrLim;
+  return t < kThrLim ? (int32_t)floor(t) : (int32_t)kThrLim;
+}
+
 __global__ void sched_scatter_kernel(const Item* __restrict__ items, int32_t n_items,
                                      const int32_t* __restrict__ P, int32_t n, int32_t q0,
                                      const int64_t* __restrict__ exclude,
-                                     int32_t* __restrict__ cursor, BItem* __restrict__ bucket) {
+                                     int32_t* __restrict__ cursor, BItem* __restrict__ bucket,
+                                     const ScreenParam* __restrict__ qpar,
+                                     const ScreenParam* __restrict__ lpar, float tau, int32_t d) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= n_items) return;
   const Item it = items[i];
@@ -233,6 +252,8 @@ __global__ void sched_scatter_kernel(const Item* __restrict__ items, int32_t n_i
   b.q = it.q;
   b.rank = it.rank;
   b.ex = exclude ? exclude[it.q] : INT64_MIN;
+  b.thr = qpar ? screen_threshold(qpar[it.q], lpar[p], tau, d) : 0;
+  b.pad = 0;
   bucket[pos] = b;
 }
 
@@ -283,6 +304,8 @@ __global__ void publish_round_kernel(const RoundCounters* __restrict__ rc,
   __hip_atomic_store(&out->sched_error, rc->sched_error, __ATOMIC_RELAXED,
                      __HIP_MEMORY_SCOPE_SYSTEM);
   __hip_atomic_store(&out->hits, rc->hits, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+  __hip_atomic_store(&out->screened, rc->screened, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+  __hip_atomic_store(&out->item_rows, rc->item_rows, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
   __threadfence_system();
 }
 
@@ -302,6 +325,8 @@ __device__ __forceinline__ void publish_from_block(const RoundCounters* rc, Roun
   __hip_atomic_store(&out->sched_error, rc->sched_error, __ATOMIC_RELAXED,
                      __HIP_MEMORY_SCOPE_SYSTEM);
   __hip_atomic_store(&out->hits, rc->hits, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+  __hip_atomic_store(&out->screened, rc->screened, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+  __hip_atomic_store(&out->item_rows, rc->item_rows, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
   __threadfence_system();
 }
 
@@ -595,10 +620,11 @@ hipError_t launch_sched_offsets(int32_t* cnt, const int64_t* list_offsets, int32
 
 hipError_t launch_sched_scatter(const Item* items, int32_t n_items, const int32_t* P, int32_t n,
                                 int32_t q0, const int64_t* exclude, int32_t* cursor,
-                                BItem* bucket, hipStream_t s) {
+                                BItem* bucket, const ScreenParam* qpar, const ScreenParam* lpar,
+                                float tau, int32_t d, hipStream_t s) {
   if (n_items <= 0) return hipSuccess;
   hipLaunchKernelGGL(sched_scatter_kernel, dim3(blocks_for(n_items)), dim3(kThreads), 0, s, items,
-                     n_items, P, n, q0, exclude, cursor, bucket);
+                     n_items, P, n, q0, exclude, cursor, bucket, qpar, lpar, tau, d);
   return hipGetLastError();
 }
 

@@ -30,7 +30,19 @@ struct Tile {
 struct BItem {
   int32_t q;
   int32_t rank;
-  int64_t ex;  // exclude_ids[q], or INT64_MIN
+  int64_t ex;   // exclude_ids[q], or INT64_MIN
+  int32_t thr;  // screened scans: smallest 8-bit product that may reach tau
+  int32_t pad;
+};
+
+// Screened scans (screen_tile.h): a list's 8-bit rows are x^ = s xi with
+// |x - x^| <= err and |x| <= norm for every row; a query's 8-bit row is
+// q^ = s qi with |q^| = norm and |q - q^| = err, both rounded up.
+struct ScreenParam {
+  float s;
+  float err;
+  float norm;
+  float pad;
 };
 
 // One qualifying candidate found by the scan (score >= tau, not excluded).
@@ -69,6 +81,7 @@ struct RoundCounters {
   unsigned long long cands;       // qualifying (query, row) pairs the scans found (whole search)
   int32_t heavy;                  // HeavyRec records claimed (whole search)
   int32_t sched_error;            // set when a round's tiles exceed the tile buffer
+  unsigned long long screened;    // pairs a screened scan scored exactly (whole search)
   // Sums of out_probes and of the qualifying candidates merged by the final
   // top-k, spread over kStatSlots counters (work-group b adds to slot
   // b % kStatSlots): thousands of adds to one address would serialise.
@@ -86,6 +99,8 @@ struct RoundSummary {
   int32_t sched_error;       // a round's tiles exceeded the tile buffer
   int32_t pad_;
   unsigned long long hits;  // pool entries written so far
+  unsigned long long screened;   // pairs the screened scans scored exactly so far
+  unsigned long long item_rows;  // (item, row) pairs scanned so far
 };
 
 // Cumulative scan counters after one round (the per-round log of a timed
@@ -177,6 +192,11 @@ struct ScanArgs {
   int32_t cand_u4;             // 16-byte offset of the LDS arena in dynamic LDS (launcher)
   int32_t arena_lds;           // LDS arena entries (launcher)
   int32_t wide;                // 1: wide configuration (one big work-group per CU)
+  // screened scans: 8-bit rows in fragment order (the partition starts of
+  // frag_offsets), 8-bit queries [nq][64 * chunks], the stored dtype
+  const void* v8 = nullptr;
+  const void* q8 = nullptr;
+  int32_t dtype = 0;
   // calibration outputs (Algorithm 3), null / 0 otherwise: per query a bitmap
   // of the ranks whose probe had a candidate, and pool entries that carry
   // the rank they were found at (Hit.q = query | rank << kRankShift)
@@ -228,9 +248,34 @@ hipError_t launch_centroid_frag(int dtype, int d, const void* centroids, int32_t
 // FragStream).  frag_rows = frag_offsets[nlist].  vector_frag_bytes is 0 for
 // dimensions the scan handles at run time (no copy).
 size_t vector_frag_bytes(int dtype, int d, int64_t frag_rows);
-hipError_t launch_vector_frag(int dtype, int d, const void* vectors, const int64_t* offsets,
-                              const int64_t* frag_offsets, int32_t nlist, int64_t frag_rows,
-                              void* frag, hipStream_t s);
+// ---- screened scan (screen_tile.h) ----
+// 64-byte chunks of an 8-bit row of d dimensions as the screened kernels take
+// it (rows are padded with zeros to one of their chunk counts), 0 where there
+// is none.
+int screen_chunks(int d);
+size_t screen_rows_bytes(int d, int64_t frag_rows);  // the 8-bit fragment-order copy
+// The copies of the stored vectors: frag (exact, fragment order; or null), v8
+// (8-bit, fragment order, with the lists' parameters lpar; or null).
+hipError_t launch_index_rows(int dtype, int d, const void* vectors, const int64_t* offsets,
+                             const int64_t* frag_offsets, int32_t nlist, int64_t frag_rows,
+                             void* frag, void* v8, ScreenParam* lpar, hipStream_t s);
+// Scores of row pairs inside kScreenSample lists ([kScreenSample * 256], -inf
+// in unused places).
+constexpr int kScreenSample = 32;
+hipError_t launch_screen_sample(int d, const void* v8, const int64_t* offsets,
+                                const int64_t* frag_offsets, int32_t nlist,
+                                const ScreenParam* lpar, float* out, hipStream_t s);
+// 8-bit copies [nq][64 * chunks] of the queries and their parameters.
+hipError_t launch_screen_queries(int dtype, int d, const void* queries, int64_t nq, void* q8,
+                                 ScreenParam* qpar, hipStream_t s);
+// Largest query tile of the screened kernels, by round kind, and the launch
+// (dense: a.tile_q > screen_tile_q(d, false) where the two differ).
+int screen_tile_q(int d, bool dense);
+int screen_grid_per_cu(int d);
+hipError_t launch_screen_scan(const ScanArgs& a, int32_t grid, hipStream_t s);
+hipError_t launch_screen_scan_reg(int nc, const ScanArgs& a, int32_t grid, hipStream_t s);
+hipError_t launch_screen_scan_lds(int nc, const ScanArgs& a, int32_t grid, hipStream_t s);
+
 // cfrag: the index's fragment-order centroids (centroid_frag_bytes > 0), or
 // null where it has none.
 hipError_t launch_rank_prefix(int dtype, const void* queries, int64_t q0, int32_t nqc,
@@ -254,9 +299,12 @@ hipError_t launch_sched_offsets(int32_t* cnt, const int64_t* list_offsets, int32
                                 int32_t row_chunk, int32_t tile_q, int32_t* item_off,
                                 int32_t* cursor, int32_t* tile_off, RoundCounters* rc,
                                 Tile* tiles, int64_t tile_cap, hipStream_t s);
+// qpar, lpar: null, or the screen parameters of the queries and the lists
+// (each bucketed item then carries its threshold).
 hipError_t launch_sched_scatter(const Item* items, int32_t n_items, const int32_t* P, int32_t n,
                                 int32_t q0, const int64_t* exclude, int32_t* cursor,
-                                BItem* bucket, hipStream_t s);
+                                BItem* bucket, const ScreenParam* qpar, const ScreenParam* lpar,
+                                float tau, int32_t d, hipStream_t s);
 hipError_t launch_sched_tiles(int32_t* cnt, const int32_t* item_off, const int32_t* tile_off,
                               const int64_t* list_offsets, int32_t nlist, int32_t row_chunk,
                               int32_t tile_q, Tile* tiles, int64_t tile_cap, hipStream_t s);
