@@ -116,7 +116,7 @@ struct sieve_index {
   // so that sieve_free_index releases all of them)
 #define SIEVE_WORKSPACE(X)                                                                 \
   X(scores) X(P) X(items) X(bucket) X(tiles) X(cnt) X(item_off) X(cursor) X(tile_off) X(rc) \
-  X(state_a) X(state_b) X(lmax) X(hcount) X(hoff) X(hcur) X(scan_tmp) X(pool)              \
+  X(state_a) X(state_b) X(lmax) X(hcount) X(hoff) X(hcur) X(pool)                          \
   X(pool_sorted) X(heavy) X(spill) X(have) X(ext) X(qext) X(Pext) X(cand) X(ccount) X(cal_idx)      \
   X(cal_q) X(cal_x) X(cal_bits) X(cal_rank) X(cal_hist) X(mix_ids) X(mix_scores)            \
   X(mix_probes) X(spec_bits) X(rlog) X(q8) X(qpar)
@@ -358,7 +358,6 @@ int grow_workspace(sieve_index* ix, const SearchPlan& pl) {
       (st = ensure(ix, ix->lmax, qn)) || (st = ensure(ix, ix->hcount, qn)) ||
       (st = ensure(ix, ix->hoff, (size_t)nq * 8)) || (st = ensure(ix, ix->hcur, (size_t)nq * 8)))
     return st;
-  if ((st = ensure(ix, ix->scan_tmp, exclusive_scan_tmp_elems(nq) * 8))) return st;
   if (pl.spec && (st = ensure(ix, ix->spec_bits, (size_t)nq * pl.hit_words * 4))) return st;
   if (pl.screen && ((st = ensure(ix, ix->q8, (size_t)nq * screen_chunks(ix->d) * 64)) ||
                     (st = ensure(ix, ix->qpar, (size_t)nq * sizeof(ScreenParam)))))
@@ -481,11 +480,6 @@ ScanArgs make_scan_args(sieve_index* ix, const void* queries, const int64_t* exc
   a.tile_q = pl.tile_q;
   a.wide = pl.wide ? 1 : 0;
   a.tau = pl.tau;
-  a.dtype = ix->dtype;
-  if (pl.screen) {
-    a.v8 = ix->v8;
-    a.q8 = ix->q8.p;
-  }
   return a;
 }
 
@@ -522,7 +516,7 @@ int run_round(sieve_index* ix, const ScanArgs& sa, int n_items, int64_t q0, cons
   HIP_TRY(launch_sched_scatter((const Item*)ix->items.p, n_items, P, pl.n, (int32_t)q0, sa.exclude,
                                (int32_t*)ix->cursor.p, (BItem*)ix->bucket.p,
                                pl.screen ? (const ScreenParam*)ix->qpar.p : nullptr,
-                               pl.screen ? ix->lpar : nullptr, pl.tau, ix->d, s));
+                               pl.screen ? ix->lpar : nullptr, pl.tau, ix->d, ix->nlist, s));
   if (!fuse)
     HIP_TRY(launch_sched_tiles((int32_t*)ix->cnt.p, (const int32_t*)ix->item_off.p,
                                (const int32_t*)ix->tile_off.p, ix->offsets, ix->nlist, chunk,
@@ -531,9 +525,14 @@ int run_round(sieve_index* ix, const ScanArgs& sa, int n_items, int64_t q0, cons
   ScanArgs sr = sa;
   sr.dynamic = scan_dynamic(ix, n_items, dense, chunk, group, grid);
   sr.tile_q = tile_q;
-  if (pl.screen)
-    HIP_TRY(launch_screen_scan(sr, grid, s));
-  else
+  if (pl.screen) {
+    ScreenArgs sc;
+    (ScanArgs&)sc = sr;
+    sc.v8 = ix->v8;
+    sc.q8 = ix->q8.p;
+    sc.dtype = ix->dtype;
+    HIP_TRY(launch_screen_scan(sc, grid, s));
+  } else
     HIP_TRY(launch_scan(ix->dtype, sr, grid, s));
   const int e2 = mark(ix, timed, s);
   span(ix, kSched, e0, e1);
@@ -831,8 +830,8 @@ int search_impl(sieve_index* ix, const void* queries, int64_t nq, const int64_t*
     }
 
     // finalize: group the pool by query, then per-query top-k
-    HIP_TRY(launch_exclusive_scan((const int32_t*)ix->hcount.p, (int64_t*)ix->hoff.p,
-                                  (int64_t*)ix->hcur.p, nq, (int64_t*)ix->scan_tmp.p, s));
+    HIP_TRY(launch_pool_segments((const int32_t*)ix->hcount.p, (int64_t*)ix->hoff.p,
+                                 (int64_t*)ix->hcur.p, nq, &rc->segs, s));
     HIP_TRY(launch_pool_scatter((const Hit*)ix->pool.p, hits, (int64_t*)ix->hcur.p,
                                 (Hit*)ix->pool_sorted.p, cal != nullptr || spec_used, s));
     const int32_t* probes_src = pl.mode == 0   ? (const int32_t*)ix->state_a.p

@@ -228,12 +228,19 @@ __global__ __launch_bounds__(NT) void rank_select_kernel(
   for (int r = t; r < n; r += NT) P[ql * ldp + r] = (int32_t)(ck[r] & 0xffffffffu);
 }
 
+// The bitwise search for the n-th largest key v may stop at any key t <= v
+// that few keys more than n reach: the candidates are then all scores >= t -
+// 2 delta, a superset of those >= v - 2 delta, and the exact order of the
+// first n is the same.  About 14 steps instead of 32, for this many more
+// candidates to sort at most.
+__device__ __forceinline__ int rank_excess(int n) { return 8 + n / 8; }
+
 // One query per block of 256 threads, its screen scores held in registers
 // (KPT per thread, nlist <= 256 * KPT): long prefixes over large centroid
 // sets, where one wave per query would hold too many keys.
-//   1. the n-th largest key is found bit by bit (32 steps; each step counts
+//   1. the n-th largest key is bounded from below bit by bit (each step counts
 //      keys >= the candidate prefix with ballot popcounts per wave and one
-//      LDS exchange between the four waves);
+//      LDS exchange between the four waves; see rank_excess);
 //   2. candidates (s32 >= v - 2 delta) are compacted with ballots into LDS;
 //   3. they are sorted by counting, near-tie runs are re-scored in fp64
 //      (waves of the block share the members), and the first n are written.
@@ -276,19 +283,22 @@ __global__ __launch_bounds__(256) void rank_select_reg_kernel(
   const double delta = 2.0 * (double)(d + 2) * 5.9604644775390625e-08 * qn * cmax + 1e-30;
   const double gap = 2.0 * delta;
 
-  // 1. exact n-th largest key (the two count slots alternate, one barrier a step)
+  // 1. a key that n keys reach (the two count slots alternate, one barrier a
+  // step; counts are sums of ballot popcounts, in scalar registers)
   uint32_t prefix = 0;
   for (int bit = 31; bit >= 0; --bit) {
     const uint32_t cand = prefix | (1u << bit);
-    int cnt = 0;  // this lane's keys >= cand, then the wave's sum
+    int cnt = 0;  // the wave's keys >= cand
 #pragma unroll
-    for (int j = 0; j < KPT; ++j) cnt += key[j] >= cand ? 1 : 0;
-    for (int o = 32; o > 0; o >>= 1) cnt += __shfl_xor(cnt, o);
+    for (int j = 0; j < KPT; ++j) cnt += __popcll(__ballot(key[j] >= cand));
     if (lane == 0) s_cnt[bit & 1][wave] = cnt;
     __syncthreads();
     const int total = s_cnt[bit & 1][0] + s_cnt[bit & 1][1] + s_cnt[bit & 1][2] +
                       s_cnt[bit & 1][3];
-    if (total >= n) prefix = cand;
+    if (total >= n) {
+      prefix = cand;
+      if (total <= n + rank_excess(n)) break;  // uniform over the block
+    }
   }
   const double lo = (double)key2f(prefix) - gap;
 
@@ -331,16 +341,22 @@ __global__ __launch_bounds__(256) void rank_select_reg_kernel(
     link[i] = l ? 1 : 0;
   }
   __syncthreads();
-  refine_members<DT>(out, cs, link, m, queries, qg, centroids, d, wave, 4);
+  // runs that start at or past n cannot change the first n
+  int me = n;
+  while (me < m && link[me - 1]) ++me;
+  refine_members<DT>(out, cs, link, me, queries, qg, centroids, d, wave, 4);
   __syncthreads();
   {
     const double gap64 =
         2.0 * 2.0 * (double)(d + (d + 63) / 64 + 6) * 1.1102230246251565e-16 * qn * cmax + 1e-300;
-    order_runs<DT>(out, cs, link, m, queries, qg, centroids, d, gap64, t, 256);
+    order_runs<DT>(out, cs, link, me, queries, qg, centroids, d, gap64, t, 256);
   }
   __syncthreads();
   for (int r = t; r < n; r += 256) P[ql * ldp + r] = (int32_t)(out[r] & 0xffffffffu);
 }
+
+// Ranks up to which the wave kernel bounds the n-th key by the lanes' maxima.
+constexpr int kLaneRanks = 40;
 
 // Boundary candidates per lane in the wave kernel (capw <= 64 * this).
 constexpr int kKeysPerLane = 8;
@@ -348,9 +364,10 @@ constexpr int kKeysPerLane = 8;
 // One query per wave, four per block; KPL = keys per lane (nlist <= 64*KPL).
 // 1. the scores of the query are held in registers, KPL per lane;
 // 2. the n-th largest key (the order-preserving integer image of the fp32
-//    score) is found bit by bit from the top: a bit is kept when at least n
-//    keys are >= the prefix with that bit set (32 counting steps, each
-//    register compares and ballot popcounts);
+//    score) is bounded from below.  Up to kLaneRanks ranks: the n-th largest
+//    of the 64 lane maxima (n lanes hold a key that reaches it; about 1.4 n
+//    keys do), found bit by bit with one ballot a step.  More ranks: bit by
+//    bit over all keys, until few more than n reach the prefix (rank_excess);
 // 3. candidates (score >= v - 2 delta) are compacted with ballots;
 // 4. they are sorted exactly by counting; near-tie runs get fp64 scores and
 //    an insertion sort, as in the block kernel.
@@ -394,15 +411,34 @@ __global__ __launch_bounds__(256) void rank_select_wave_kernel(
   const double delta = 2.0 * (double)(d + 2) * 5.9604644775390625e-08 * qn * cmax + 1e-30;
   const double gap = 2.0 * delta;
 
-  // 2. exact n-th largest key; each count is a sum of ballot popcounts, so
+  // 2. a key that n keys reach; each count is a sum of ballot popcounts, so
   // it stays in scalar registers (no cross-lane shuffles)
   uint32_t prefix = 0;
-  for (int bit = 31; bit >= 0; --bit) {
-    const uint32_t cand = prefix | (1u << bit);
-    int cnt = 0;
+  int reach = 0x7fffffff;  // keys that reach the prefix of the lane maxima
+  if (n <= kLaneRanks && nlist >= 64) {
+    uint32_t kmax = key[0];
 #pragma unroll
-    for (int j = 0; j < KPL; ++j) cnt += __popcll(__ballot(key[j] >= cand));
-    if (cnt >= n) prefix = cand;
+    for (int j = 1; j < KPL; ++j) kmax = max(kmax, key[j]);
+    for (int bit = 31; bit >= 0; --bit) {
+      const uint32_t cand = prefix | (1u << bit);
+      if (__popcll(__ballot(kmax >= cand)) >= n) prefix = cand;
+    }
+    reach = 0;
+#pragma unroll
+    for (int j = 0; j < KPL; ++j) reach += __popcll(__ballot(key[j] >= prefix));
+  }
+  if (reach > n + 64) {  // more ranks, or large keys crowded on few lanes
+    prefix = 0;
+    for (int bit = 31; bit >= 0; --bit) {
+      const uint32_t cand = prefix | (1u << bit);
+      int cnt = 0;
+#pragma unroll
+      for (int j = 0; j < KPL; ++j) cnt += __popcll(__ballot(key[j] >= cand));
+      if (cnt >= n) {
+        prefix = cand;
+        if (cnt <= n + rank_excess(n)) break;
+      }
+    }
   }
   const double lo = (double)key2f(prefix) - gap;
 
@@ -462,6 +498,9 @@ hipError_t launch_wave(const void* queries, int64_t q0, int32_t nqc, const void*
                        hipStream_t s) {
   if (nlist <= 256)
     return launch_wave_t<DT, 4>(queries, q0, nqc, centroids, nlist, d, scores, n, capw, cmax,
+                                  P, ldp, rc, s);
+  if (nlist <= 512)
+    return launch_wave_t<DT, 8>(queries, q0, nqc, centroids, nlist, d, scores, n, capw, cmax,
                                   P, ldp, rc, s);
   if (nlist <= 1024)
     return launch_wave_t<DT, 16>(queries, q0, nqc, centroids, nlist, d, scores, n, capw, cmax,

@@ -84,11 +84,20 @@ __device__ __forceinline__ void refine_members(unsigned long long* ck, double* c
                                                const uint8_t* link, int m,
                                                const void* queries, int64_t qg,
                                                const void* centroids, int d, int wave, int nwaves) {
-  for (int i = wave; i < m; i += nwaves) {
-    const bool member = link[i] || (i > 0 && link[i - 1]);  // wave-uniform
-    if (member) {
-      const double v = wave_dot_fp64<DT>(queries, qg, centroids, (int)(ck[i] & 0xffffffffu), d);
-      if ((threadIdx.x & 63) == 0) cs[i] = v;
+  // members are few: a ballot finds them 64 positions at a time (a walk over
+  // the positions, one LDS round trip each, took longer than their products)
+  const int lane = threadIdx.x & 63;
+  int turn = 0;
+  for (int b = 0; b < m; b += 64) {
+    const int i = b + lane;
+    unsigned long long mem = __ballot(i < m && (link[i] || (i > 0 && link[i - 1])));
+    for (; mem; mem &= mem - 1) {
+      if (turn == wave) {
+        const int x = b + __builtin_ctzll(mem);
+        const double v = wave_dot_fp64<DT>(queries, qg, centroids, (int)(ck[x] & 0xffffffffu), d);
+        if (lane == 0) cs[x] = v;
+      }
+      turn = turn + 1 == nwaves ? 0 : turn + 1;
     }
   }
 }

@@ -49,23 +49,22 @@ __global__ __launch_bounds__(kInitThreads) void emit_initial_kernel(
   extern __shared__ int32_t s_hist[];  // [nlist]
   for (int i = threadIdx.x; i < nlist; i += blockDim.x) s_hist[i] = 0;
   __syncthreads();
-  for (int64_t ql = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; ql < nqc;
-       ql += (int64_t)gridDim.x * blockDim.x) {
-    const int32_t q = q0 + (int32_t)ql;
-    for (int j = 0; j < s0; ++j) {
-      Item it;
-      it.q = q;
-      it.rank = j;
-      if (ql * s0 + j < item_cap) items[ql * s0 + j] = it;
-      atomicAdd(&s_hist[P[ql * n + j]], 1);
-    }
-    if (mode == 0) {
-      state_a[q] = s0;
-      state_b[q] = s0;  // ranks issued (speculative issue)
-      lmax[q] = 0;
-    } else if (mode == 1) {
-      state_a[q] = 0;  // next (0-based rank in flight)
-      state_b[q] = 0;  // stale
+  const int64_t step = (int64_t)gridDim.x * blockDim.x;
+  const int64_t first = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  // one thread per item: a wave reads the consecutive ranks of a query (one
+  // thread per query would read 64 rows of P at once: 377 us for 5.1M items
+  // of 256 ranks, now 23)
+  for (int64_t i = first; i < nqc * s0; i += step) {
+    const int64_t ql = i / s0;
+    const int j = (int)(i - ql * s0);
+    if (i < item_cap) items[i] = Item{q0 + (int32_t)ql, j};
+    atomicAdd(&s_hist[P[ql * n + j]], 1);
+  }
+  if (mode != 2) {
+    for (int64_t ql = first; ql < nqc; ql += step) {
+      const int64_t q = q0 + ql;
+      state_a[q] = mode == 0 ? s0 : 0;  // stop line, or the rank in flight
+      state_b[q] = mode == 0 ? s0 : 0;  // ranks issued, or stale probes
       lmax[q] = 0;
     }
   }
@@ -97,8 +96,8 @@ __global__ __launch_bounds__(kOffThreads) void sched_offsets_kernel(
     int32_t row_chunk, int32_t tile_q, int32_t* __restrict__ item_off,
     int32_t* __restrict__ cursor, int32_t* __restrict__ tile_off, RoundCounters* rc,
     Tile* __restrict__ tiles, int64_t tile_cap) {
-  __shared__ int64_t s_items[kOffThreads];
-  __shared__ int64_t s_tiles[kOffThreads];
+  __shared__ int64_t s_items[kOffThreads / 64];
+  __shared__ int64_t s_tiles[kOffThreads / 64];
   __shared__ unsigned long long s_stat[3];
   // every list's item count and length (rows < 2^31, checked at load) in
   // LDS: the loads are coalesced and all in flight at once, and each thread
@@ -147,19 +146,33 @@ __global__ __launch_bounds__(kOffThreads) void sched_offsets_kernel(
     }
   }
   if (t < 3) s_stat[t] = 0;
-  s_items[t] = si;
-  s_tiles[t] = st;
-  __syncthreads();
-  // inclusive Hillis-Steele scan over the 1024 partial sums
-  for (int off = 1; off < kOffThreads; off <<= 1) {
-    int64_t vi = t >= off ? s_items[t - off] : 0;
-    int64_t vt = t >= off ? s_tiles[t - off] : 0;
-    __syncthreads();
-    s_items[t] += vi;
-    s_tiles[t] += vt;
-    __syncthreads();
+  // exclusive prefixes of the threads' sums: over the wave's lanes, then over
+  // the waves
+  const int lane = t & 63;
+  int64_t vi = si, vt = st;
+#pragma unroll
+  for (int o = 1; o < 64; o <<= 1) {
+    const int64_t ui = __shfl_up(vi, o), ut = __shfl_up(vt, o);
+    if (lane >= o) {
+      vi += ui;
+      vt += ut;
+    }
   }
-  int64_t ri = s_items[t] - si, rt = s_tiles[t] - st;  // exclusive prefixes
+  if (lane == 63) {
+    s_items[t >> 6] = vi;
+    s_tiles[t >> 6] = vt;
+  }
+  __syncthreads();
+  int64_t ri = vi - si, rt = vt - st, all_tiles = 0;
+#pragma unroll
+  for (int w = 0; w < kOffThreads / 64; ++w) {
+    const int64_t wi = s_items[w], wt = s_tiles[w];
+    if (w < (t >> 6)) {
+      ri += wi;
+      rt += wt;
+    }
+    all_tiles += wt;
+  }
   for (int p = b; p < e; ++p) {
     const int64_t len = s_l[p];
     const int c = s_c[p];
@@ -208,11 +221,12 @@ __global__ __launch_bounds__(kOffThreads) void sched_offsets_kernel(
   if (t == 0) {
     // a tile count past the buffer (never, by the host's bound) runs no scan
     // and fails the search
-    const int64_t nt = s_tiles[kOffThreads - 1];
+    const int64_t nt = all_tiles;
     rc->ntiles = nt <= tile_cap ? (int32_t)nt : 0;
     if (nt > tile_cap) rc->sched_error = 1;
     rc->new_items = 0;
     rc->n_ext = 0;
+    rc->updated = 0;
     for (int x = 0; x < 8; ++x) rc->queue[x] = 0;
     rc->list_rows += s_stat[0];
     rc->item_rows += s_stat[1];
@@ -255,6 +269,52 @@ __global__ void sched_scatter_kernel(const Item* __restrict__ items, int32_t n_i
   b.thr = qpar ? screen_threshold(qpar[it.q], lpar[p], tau, d) : 0;
   b.pad = 0;
   bucket[pos] = b;
+}
+
+// Many items per list: a work-group takes kGroupItems consecutive items,
+// counts them by list in LDS and claims each list's slots once (one-address
+// atomics serialise: 400,000 items over 512 lists took 124 us item by item,
+// now 20 us).  The order inside a list's bucket is free.
+constexpr int kGroupThreads = 1024;
+constexpr int kGroupPer = 4;
+constexpr int kGroupItems = kGroupThreads * kGroupPer;
+
+__global__ __launch_bounds__(kGroupThreads) void sched_scatter_grouped_kernel(
+    const Item* __restrict__ items, int32_t n_items, const int32_t* __restrict__ P, int32_t n,
+    int32_t q0, const int64_t* __restrict__ exclude, int32_t* __restrict__ cursor,
+    BItem* __restrict__ bucket, const ScreenParam* __restrict__ qpar,
+    const ScreenParam* __restrict__ lpar, float tau, int32_t d, int32_t nlist) {
+  extern __shared__ int32_t s_cnt[];  // [nlist]: the group's items, then its first slot
+  for (int i = threadIdx.x; i < nlist; i += kGroupThreads) s_cnt[i] = 0;
+  __syncthreads();
+  const int64_t i0 = (int64_t)blockIdx.x * kGroupItems + threadIdx.x;
+  Item it[kGroupPer];
+  int p[kGroupPer], at[kGroupPer];
+#pragma unroll
+  for (int u = 0; u < kGroupPer; ++u) {
+    const int64_t i = i0 + (int64_t)u * kGroupThreads;
+    it[u] = items[i < n_items ? i : n_items - 1];
+  }
+#pragma unroll
+  for (int u = 0; u < kGroupPer; ++u) p[u] = P[(int64_t)(it[u].q - q0) * n + it[u].rank];
+#pragma unroll
+  for (int u = 0; u < kGroupPer; ++u)
+    at[u] = i0 + (int64_t)u * kGroupThreads < n_items ? atomicAdd(&s_cnt[p[u]], 1) : -1;
+  __syncthreads();
+  for (int i = threadIdx.x; i < nlist; i += kGroupThreads)
+    if (const int c = s_cnt[i]) s_cnt[i] = atomicAdd(&cursor[i], c);
+  __syncthreads();
+#pragma unroll
+  for (int u = 0; u < kGroupPer; ++u) {
+    if (at[u] < 0) continue;
+    BItem b;
+    b.q = it[u].q;
+    b.rank = it[u].rank;
+    b.ex = exclude ? exclude[it[u].q] : INT64_MIN;
+    b.thr = qpar ? screen_threshold(qpar[it[u].q], lpar[p[u]], tau, d) : 0;
+    b.pad = 0;
+    bucket[s_cnt[p[u]] + at[u]] = b;
+  }
 }
 
 // One thread per list: write its tiles (query tiles x row chunks), tiles that
@@ -309,12 +369,18 @@ __global__ void publish_round_kernel(const RoundCounters* __restrict__ rc,
   __threadfence_system();
 }
 
-// The summary written by the update launch itself when it is one work-group:
-// the counter updates the summary reads (new_items, n_ext) are atomics whose
-// results their threads consumed before the barrier, so they are done.
-__device__ __forceinline__ void publish_from_block(const RoundCounters* rc, RoundSummary* out) {
+// The summary written by the update launch itself, by its last work-group.
+// What it reads are counters that only device-scope atomics change: each
+// thread's are done (waited for) before its work-group counts itself, so no
+// release fence is needed (a fence per thread writes back L2).  Past
+// kPublishBlocks work-groups the count on one address takes longer than a
+// launch of its own.
+constexpr int kPublishBlocks = 128;
+__device__ __forceinline__ void publish_from_last(RoundCounters* rc, RoundSummary* out) {
+  __builtin_amdgcn_s_waitcnt(0);
   __syncthreads();
   if (threadIdx.x != 0) return;
+  if (gridDim.x > 1 && atomicAdd(&rc->updated, 1) != (int32_t)gridDim.x - 1) return;
   const int32_t ni = __hip_atomic_load(&rc->new_items, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   const int32_t ne = __hip_atomic_load(&rc->n_ext, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   __hip_atomic_store(&out->new_items, ni, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
@@ -447,7 +513,7 @@ __global__ void update_lookahead_kernel(int64_t nq, const int32_t* __restrict__ 
       atomicAdd(&cnt[P[q * n + e0 + j]], 1);
     }
   }
-  if (out) publish_from_block(rc, out);  // one work-group only
+  if (out) publish_from_last(rc, out);
 }
 
 // next[q]: rank in flight (0-based) or -1 once stopped; on stopping,
@@ -492,7 +558,7 @@ __global__ void update_basic_kernel(int64_t nq, const int32_t* __restrict__ P, i
                                     RoundCounters* rc, RoundSummary* out) {
   const int64_t q = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (q < nq) basic_one(q, P, n, W, next, stale, lmax, have, ext, items, item_cap, cnt, rc);
-  if (out) publish_from_block(rc, out);  // one work-group only
+  if (out) publish_from_last(rc, out);
 }
 
 // Row copy in 16-byte units: dst row i <- src row ext[i].
@@ -596,7 +662,7 @@ hipError_t launch_emit_initial(const int32_t* P, int32_t n, int64_t nqc, int32_t
                                int32_t nlist, int32_t* state_a, int32_t* state_b, int32_t* lmax, hipStream_t s) {
   if (nqc <= 0) return hipSuccess;
   if (nlist < 1 || nlist > kMaxNlist) return hipErrorInvalidValue;
-  const int b = std::min(blocks_for(nqc, kInitThreads), kInitBlocksMax);
+  const int b = std::min(blocks_for(nqc * s0, 4 * kInitThreads), kInitBlocksMax);
   hipLaunchKernelGGL(emit_initial_kernel, dim3(b), dim3(kInitThreads), (size_t)nlist * 4, s, P,
                      n, nqc, q0, s0, mode, items, item_cap, cnt, nlist, state_a, state_b, lmax);
   return hipGetLastError();
@@ -621,8 +687,17 @@ hipError_t launch_sched_offsets(int32_t* cnt, const int64_t* list_offsets, int32
 hipError_t launch_sched_scatter(const Item* items, int32_t n_items, const int32_t* P, int32_t n,
                                 int32_t q0, const int64_t* exclude, int32_t* cursor,
                                 BItem* bucket, const ScreenParam* qpar, const ScreenParam* lpar,
-                                float tau, int32_t d, hipStream_t s) {
+                                float tau, int32_t d, int32_t nlist, hipStream_t s) {
   if (n_items <= 0) return hipSuccess;
+  // worth it where a group holds several items of a list; the LDS histogram
+  // (64 KB at most) needs no opt-in
+  if (n_items >= 8 * kGroupItems && nlist <= kGroupItems / 2) {
+    hipLaunchKernelGGL(sched_scatter_grouped_kernel,
+                       dim3((n_items + kGroupItems - 1) / kGroupItems), dim3(kGroupThreads),
+                       (size_t)nlist * 4, s, items, n_items, P, n, q0, exclude, cursor, bucket,
+                       qpar, lpar, tau, d, nlist);
+    return hipGetLastError();
+  }
   hipLaunchKernelGGL(sched_scatter_kernel, dim3(blocks_for(n_items)), dim3(kThreads), 0, s, items,
                      n_items, P, n, q0, exclude, cursor, bucket, qpar, lpar, tau, d);
   return hipGetLastError();
@@ -647,8 +722,8 @@ hipError_t launch_update_lookahead(int64_t nq, const int32_t* P, int32_t n, int3
   hipLaunchKernelGGL(update_lookahead_kernel, dim3(blocks_for(nq)), dim3(kThreads), 0, s, nq, P, n,
                      W, stop, lmax, have, ext, items, item_cap, cnt, rc, hitbits, words, issued,
                      spec_max,
-                     spec_min, blocks_for(nq) == 1 ? out : nullptr);
-  if (out && blocks_for(nq) > 1)
+                     spec_min, blocks_for(nq) <= kPublishBlocks ? out : nullptr);
+  if (out && blocks_for(nq) > kPublishBlocks)
     hipLaunchKernelGGL(publish_round_kernel, dim3(1), dim3(64), 0, s, rc, out);
   return hipGetLastError();
 }
@@ -659,8 +734,8 @@ hipError_t launch_update_basic(int64_t nq, const int32_t* P, int32_t n, int32_t 
                                RoundSummary* out, hipStream_t s) {
   hipLaunchKernelGGL(update_basic_kernel, dim3(blocks_for(nq)), dim3(kThreads), 0, s, nq, P, n, W,
                      next, stale, lmax, have, ext, items, item_cap, cnt, rc,
-                     blocks_for(nq) == 1 ? out : nullptr);
-  if (out && blocks_for(nq) > 1)
+                     blocks_for(nq) <= kPublishBlocks ? out : nullptr);
+  if (out && blocks_for(nq) > kPublishBlocks)
     hipLaunchKernelGGL(publish_round_kernel, dim3(1), dim3(64), 0, s, rc, out);
   return hipGetLastError();
 }

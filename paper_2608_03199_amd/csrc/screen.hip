@@ -349,7 +349,7 @@ int screen_tile_q(int d, bool dense) {
 
 int screen_grid_per_cu(int d) { return screen_chunks(d) <= 2 ? 2 : 1; }
 
-hipError_t launch_screen_scan(const ScanArgs& a, int32_t grid, hipStream_t s) {
+hipError_t launch_screen_scan(const ScreenArgs& a, int32_t grid, hipStream_t s) {
   const int nc = screen_chunks(a.d);
   if (nc == 0 || !a.v8 || !a.q8 || !a.frag_offsets || !a.arena_on) return hipErrorInvalidValue;
   return nc <= 2 ? launch_screen_scan_reg(nc, a, grid, s) : launch_screen_scan_lds(nc, a, grid, s);

@@ -4,7 +4,7 @@
 
 namespace sieve {
 
-hipError_t launch_screen_scan_lds(int nc, const ScanArgs& a, int32_t grid, hipStream_t s) {
+hipError_t launch_screen_scan_lds(int nc, const ScreenArgs& a, int32_t grid, hipStream_t s) {
   switch (nc) {
     case 3: return launch_screen_k<3, false, 8, 512, 1>(a, grid, s);
     case 4: return launch_screen_k<4, false, 8, 512, 1>(a, grid, s);

@@ -207,7 +207,7 @@ __device__ __forceinline__ void stream_screen_lds(const u32x4* __restrict__ lds,
 // tau stay, compacted in order; returns their number.  Bound by the latency
 // of the gathered row and query reads: two groups of pairs are in flight.
 template <int DT>
-__device__ __forceinline__ int rescore_pairs(TileSpill* ent, int n, const ScanArgs& a, int64_t r0,
+__device__ __forceinline__ int rescore_pairs(TileSpill* ent, int n, const ScreenArgs& a, int64_t r0,
                                              const int32_t* sq) {
   const int lane = threadIdx.x & 63;
   const int h = lane >> 4, r16 = lane & 15;
@@ -319,7 +319,7 @@ __device__ __forceinline__ void with_blocks(int qb_n, F&& f) {
 // t runs, the items of t + 1, the record of t + 2 and the claim of t + 3 load;
 // the queries of t + 1 stage under t's end.
 template <int NC, bool kReg, int kMaxQB, int kNT, int kOcc>
-__global__ __launch_bounds__(kNT, kOcc) void screen_scan_kernel(ScanArgs a) {
+__global__ __launch_bounds__(kNT, kOcc) void screen_scan_kernel(ScreenArgs a) {
   constexpr int kTQ = 16 * kMaxQB;
   constexpr int kSegs = 4 * NC + 1;
   extern __shared__ u32x4 lds[];
@@ -526,7 +526,7 @@ __global__ __launch_bounds__(kNT, kOcc) void screen_scan_kernel(ScanArgs a) {
 constexpr int kScreenDynLds = 150 * 1024;
 
 template <int NC, bool kReg, int kMaxQB, int kNT, int kOcc>
-hipError_t launch_screen_k(ScanArgs a, int32_t grid, hipStream_t s) {
+hipError_t launch_screen_k(ScreenArgs a, int32_t grid, hipStream_t s) {
   static const size_t dyn_max = [] {
     hipFuncAttributes fa{};
     int dev = 0, per_block = 0;

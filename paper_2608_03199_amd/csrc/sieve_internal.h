@@ -74,6 +74,9 @@ struct RoundCounters {
   int32_t queue[8];        // per-XCD tile cursors of the scan's work queue
   int32_t rank_error;      // set when a rank boundary has more than kMaxCand candidates
   int32_t n_ext;           // queries whose stop line passed their ranked prefix (this round)
+  int32_t updated;         // work-groups of this round's update that are done
+  int32_t pad_;
+  unsigned long long segs; // pool segments handed out to queries by the finalize
   unsigned long long list_rows;   // sum over active lists of their length (this round)
   unsigned long long item_rows;   // sum over items of their list's length (this round)
   unsigned long long list_loads;  // active non-empty lists (this round)
@@ -192,17 +195,20 @@ struct ScanArgs {
   int32_t cand_u4;             // 16-byte offset of the LDS arena in dynamic LDS (launcher)
   int32_t arena_lds;           // LDS arena entries (launcher)
   int32_t wide;                // 1: wide configuration (one big work-group per CU)
-  // screened scans: 8-bit rows in fragment order (the partition starts of
-  // frag_offsets), 8-bit queries [nq][64 * chunks], the stored dtype
-  const void* v8 = nullptr;
-  const void* q8 = nullptr;
-  int32_t dtype = 0;
   // calibration outputs (Algorithm 3), null / 0 otherwise: per query a bitmap
   // of the ranks whose probe had a candidate, and pool entries that carry
   // the rank they were found at (Hit.q = query | rank << kRankShift)
   uint32_t* hitbits = nullptr;
   int32_t hit_words = 0;       // 32-bit words per query in hitbits
   float tau;
+};
+
+struct ScreenArgs : ScanArgs {
+  // screened scans: 8-bit rows in fragment order (the partition starts of
+  // frag_offsets), 8-bit queries [nq][64 * chunks], the stored dtype
+  const void* v8 = nullptr;
+  const void* q8 = nullptr;
+  int32_t dtype = 0;
 };
 
 // Query rows per tile for a dtype and dimension: as many 16-row blocks (<= 8)
@@ -272,9 +278,9 @@ hipError_t launch_screen_queries(int dtype, int d, const void* queries, int64_t 
 // (dense: a.tile_q > screen_tile_q(d, false) where the two differ).
 int screen_tile_q(int d, bool dense);
 int screen_grid_per_cu(int d);
-hipError_t launch_screen_scan(const ScanArgs& a, int32_t grid, hipStream_t s);
-hipError_t launch_screen_scan_reg(int nc, const ScanArgs& a, int32_t grid, hipStream_t s);
-hipError_t launch_screen_scan_lds(int nc, const ScanArgs& a, int32_t grid, hipStream_t s);
+hipError_t launch_screen_scan(const ScreenArgs& a, int32_t grid, hipStream_t s);
+hipError_t launch_screen_scan_reg(int nc, const ScreenArgs& a, int32_t grid, hipStream_t s);
+hipError_t launch_screen_scan_lds(int nc, const ScreenArgs& a, int32_t grid, hipStream_t s);
 
 // cfrag: the index's fragment-order centroids (centroid_frag_bytes > 0), or
 // null where it has none.
@@ -304,7 +310,7 @@ hipError_t launch_sched_offsets(int32_t* cnt, const int64_t* list_offsets, int32
 hipError_t launch_sched_scatter(const Item* items, int32_t n_items, const int32_t* P, int32_t n,
                                 int32_t q0, const int64_t* exclude, int32_t* cursor,
                                 BItem* bucket, const ScreenParam* qpar, const ScreenParam* lpar,
-                                float tau, int32_t d, hipStream_t s);
+                                float tau, int32_t d, int32_t nlist, hipStream_t s);
 hipError_t launch_sched_tiles(int32_t* cnt, const int32_t* item_off, const int32_t* tile_off,
                               const int64_t* list_offsets, int32_t nlist, int32_t row_chunk,
                               int32_t tile_q, Tile* tiles, int64_t tile_cap, hipStream_t s);
@@ -354,9 +360,10 @@ struct FillSegs {
 };
 hipError_t launch_fill_multi(const FillSegs& f, hipStream_t s);
 hipError_t launch_zero_bytes(void* p, int64_t bytes, hipStream_t s);
-hipError_t launch_exclusive_scan(const int32_t* in, int64_t* out, int64_t* out_copy, int64_t n,
-                                 int64_t* block_tmp, hipStream_t s);
-size_t exclusive_scan_tmp_elems(int64_t n);
+// Segments of the grouped pool: off[q] = cursor[q] = the first of cnt[q]
+// consecutive places, in some order of the queries (*next counts places).
+hipError_t launch_pool_segments(const int32_t* cnt, int64_t* off, int64_t* cursor, int64_t nq,
+                                unsigned long long* next, hipStream_t s);
 // Exact top-k pass over the overflowed (tile, query) groups: one wave per
 // HeavyRec selects each query's top k (score desc, id asc) among the tile's
 // qualifying rows and appends them to the pool.
