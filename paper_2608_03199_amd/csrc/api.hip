@@ -495,7 +495,7 @@ int run_round(sieve_index* ix, const ScanArgs& sa, int n_items, int64_t q0, cons
   if (pl.screen) {
     chunk = dense ? pl.s_chunk_dense : pl.s_chunk;
     group = tile_q = screen_tile_q(ix->d, dense);
-    grid = ((ix->cus * screen_grid_per_cu(ix->d) + 7) / 8) * 8;
+    grid = ((ix->cus * screen_grid_per_cu(ix->d, dense) + 7) / 8) * 8;
   } else if (pl.rega) {
     // dense rounds: 128-query tiles of whole lists, one work-group per CU;
     // sparse rounds: 64-query tiles of 512 rows, two per CU
@@ -531,6 +531,10 @@ int run_round(sieve_index* ix, const ScanArgs& sa, int n_items, int64_t q0, cons
     sc.v8 = ix->v8;
     sc.q8 = ix->q8.p;
     sc.dtype = ix->dtype;
+    // the spill buffer's share of each work-group (an even entry count)
+    while (sc.spill_cap > 0 &&
+           (size_t)grid * arena_block_entries(sc.spill_cap) * sizeof(TileSpill) > ix->spill.bytes)
+      sc.spill_cap = sc.spill_cap / 4 * 2;
     HIP_TRY(launch_screen_scan(sc, grid, s));
   } else
     HIP_TRY(launch_scan(ix->dtype, sr, grid, s));

@@ -341,13 +341,15 @@ hipError_t launch_screen_queries(int dtype, int d, const void* queries, int64_t 
   return hipGetLastError();
 }
 
+// 112 queries where two work-groups of 128 would pass a CU's LDS.
 int screen_tile_q(int d, bool dense) {
-  const int nc = screen_chunks(d);
-  if (nc <= 2) return dense ? 128 : 64;
-  return 128;
+  return !dense ? 64 : (screen_chunks(d) == 8 ? 112 : 128);
 }
 
-int screen_grid_per_cu(int d) { return screen_chunks(d) <= 2 ? 2 : 1; }
+int screen_grid_per_cu(int d, bool dense) {
+  const int nc = screen_chunks(d);
+  return dense && nc > 8 ? 1 : 2;
+}
 
 hipError_t launch_screen_scan(const ScreenArgs& a, int32_t grid, hipStream_t s) {
   const int nc = screen_chunks(a.d);

@@ -4,9 +4,8 @@
 
 namespace sieve {
 
-// Dense rounds: tiles of up to 128 queries, one work-group per CU with the
-// whole register file (a deep row ring); sparse rounds: up to 64 queries,
-// two work-groups per CU.
+// Dense rounds: tiles of up to 128 queries, two work-groups per CU; sparse
+// rounds: up to 64 queries, as many.
 hipError_t launch_screen_scan_reg(int nc, const ScreenArgs& a, int32_t grid, hipStream_t s) {
   const bool dense = a.tile_q > 64;
   if (nc == 1)

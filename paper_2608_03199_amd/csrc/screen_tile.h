@@ -51,19 +51,32 @@ __device__ __forceinline__ const char* block_ptr(const char* frag, int nblk, int
   return frag + (size_t)b * (NC * 1024);
 }
 
+// Whether some pair of the row block passes (uniform); mq: the largest sum of
+// each query block, for cand to skip the blocks without a pair.
+template <int QB>
+__device__ __forceinline__ bool vote_blocks(const i32x4 (&acc)[QB], int (&mq)[QB]) {
+  int mx = -1;
+#pragma unroll
+  for (int qb = 0; qb < QB; ++qb) {
+    mq[qb] = max(max(acc[qb][0], acc[qb][1]), max(acc[qb][2], acc[qb][3]));
+    mx = max(mx, mq[qb]);
+  }
+  return __ballot(mx >= 0) != 0ull;
+}
+
 // Ring depth (row blocks) of the register-held stream: the fragments of the
 // queries take 4 NC QB registers, the accumulator starts and the accumulators
 // 4 QB each.
 template <int NC, int QB, int kRegs>
 constexpr int screen_ring() {
-  const int nb = (kRegs - 4 * NC * QB - 8 * QB - 96) / (4 * NC);
+  const int nb = (kRegs - 4 * NC * QB - 8 * QB - (kRegs > 128 ? 96 : 48)) / (4 * NC);
   return nb < 3 ? 3 : (nb > 8 ? 8 : nb);
 }
 
 // Query fragments in registers (rows of at most two chunks).  Per step: the
 // MFMAs of one row block, then its vote; the vote's latency is hidden by the
-// other waves of the SIMD.  cand(acc, blk) runs for blocks that hold a
-// passing pair; when it cannot take a block it sets resume >= 0 and the
+// other waves of the SIMD.  cand(acc, mq, blk) runs for blocks that
+// hold a passing pair; when it cannot take a block it sets resume >= 0 and the
 // stream ends.
 template <int NC, int QB, int kRegs, typename Cand>
 __device__ __forceinline__ void stream_screen_reg(const u32x4* __restrict__ lds, int segs,
@@ -112,13 +125,8 @@ __device__ __forceinline__ void stream_screen_reg(const u32x4* __restrict__ lds,
 #pragma unroll
       for (int qb = 0; qb < QB; ++qb) acc[qb] = mma_i8(qf[c][qb], buf[j][c], acc[qb]);
     }
-    int mx = acc[0][0];
-#pragma unroll
-    for (int qb = 0; qb < QB; ++qb) {
-#pragma unroll
-      for (int r = 0; r < 4; ++r) mx = max(mx, acc[qb][r]);
-    }
-    if (__ballot(mx >= 0) != 0ull) cand(acc, blk);
+    int mq[QB];
+    if (vote_blocks(acc, mq)) cand(acc, mq, blk);
     blk += nw;
   };
   // whole trips of NB steps (blocks past the last are not taken by cand)
@@ -187,13 +195,8 @@ __device__ __forceinline__ void stream_screen_lds(const u32x4* __restrict__ lds,
         }
       }
       if (s == NS - 1) {
-        int mx = acc[0][0];
-#pragma unroll
-        for (int qb = 0; qb < QB; ++qb) {
-#pragma unroll
-          for (int r = 0; r < 4; ++r) mx = max(mx, acc[qb][r]);
-        }
-        if (__ballot(mx >= 0) != 0ull) cand(acc, blk);
+        int mq[QB];
+        if (vote_blocks(acc, mq)) cand(acc, mq, blk);
       }
     }
     rb += NB * nw;
@@ -427,22 +430,24 @@ __global__ __launch_bounds__(kNT, kOcc) void screen_scan_kernel(ScreenArgs a) {
     int first = wv, first_qb = 0;      // where the stream starts or resumes
     for (;;) {
       int resume = -1;                 // (block << 5 | query block) that did not fit
-      auto cand = [&](const auto& acc, int blk) {
+      // Half of a near-duplicate tile's blocks come here: one compare per
+      // query block, then one per element of the blocks with a pair; the
+      // lanes of an element's mask take consecutive slots.
+      auto cand = [&](const auto& acc, const auto& mq, int blk) {
         constexpr int QB = sizeof(acc) / sizeof(acc[0]);
         if (blk >= nblk || blk < first || resume >= 0) return;
-        const bool rok = blk * 16 + r16 < nrows;
+        const unsigned long long rows =
+            blk * 16 + 16 <= nrows ? ~0ull : __ballot(blk * 16 + r16 < nrows);
         const int qmin = blk == first ? first_qb : 0;
-        const uint32_t roff = (uint32_t)(blk * 16 + r16);
+        const uint32_t roff = (uint32_t)(blk * 16 + r16) | (uint32_t)(4 * h) << kSpillRowBits;
 #pragma unroll
         for (int qb = 0; qb < QB; ++qb) {
-          const i32x4 v = acc[qb];
-          const bool okq = rok && max(max(v[0], v[1]), max(v[2], v[3])) >= 0;
-          if (__ballot(okq) == 0ull || qb < qmin || resume >= 0) continue;
+          if ((__ballot(mq[qb] >= 0) & rows) == 0ull || qb < qmin || resume >= 0) continue;
           unsigned long long m[4];
           int tot = 0;
 #pragma unroll
           for (int r = 0; r < 4; ++r) {
-            m[r] = __ballot(rok && v[r] >= 0);
+            m[r] = __ballot(acc[qb][r] >= 0) & rows;
             tot += __popcll(m[r]);
           }
           if (wcnt + tot > wcap) {
@@ -451,11 +456,12 @@ __global__ __launch_bounds__(kNT, kOcc) void screen_scan_kernel(ScreenArgs a) {
           }
 #pragma unroll
           for (int r = 0; r < 4; ++r) {
-            if (rok && v[r] >= 0)
+            if (m[r] == 0ull) continue;
+            if ((m[r] >> lane) & 1ull)
               mine[wcnt + (int)__builtin_amdgcn_mbcnt_hi(
                               (uint32_t)(m[r] >> 32),
                               __builtin_amdgcn_mbcnt_lo((uint32_t)m[r], 0u))] =
-                  TileSpill{0.f, roff | ((uint32_t)(qb * 16 + 4 * h + r) << kSpillRowBits)};
+                  TileSpill{0.f, roff + ((uint32_t)(qb * 16 + r) << kSpillRowBits)};
             wcnt += __popcll(m[r]);
           }
         }
@@ -463,7 +469,7 @@ __global__ __launch_bounds__(kNT, kOcc) void screen_scan_kernel(ScreenArgs a) {
       with_blocks<1, kMaxQB>((nq + 15) >> 4, [&](auto qbc) {
         constexpr int QB = decltype(qbc)::value;
         if constexpr (kReg)
-          stream_screen_reg<NC, QB, (kNT / 256 * kOcc == 1 ? 512 : 256)>(
+          stream_screen_reg<NC, QB, 512 / (kNT / 256 * kOcc)>(
               lds, kSegs, s_init[set], frag, nblk, first, nwv, resume, cand);
         else
           stream_screen_lds<NC, QB>(lds, kSegs, s_init[set], frag, nblk, first, nwv, resume, cand);
@@ -521,9 +527,11 @@ __global__ __launch_bounds__(kNT, kOcc) void screen_scan_kernel(ScreenArgs a) {
   if (lane == 0 && passed) atomicAdd(&a.rc->screened, passed);
 }
 
-// Dynamic LDS: the staged queries, then the arena (at least 256 entries per
-// wave: one 16 x 16 block of passing pairs always fits an empty part).
+// Dynamic LDS: the staged queries, then the arena (at least kArenaWaveMin
+// entries per wave: a wave's pairs of one query block always fit an empty
+// part).
 constexpr int kScreenDynLds = 150 * 1024;
+constexpr int kArenaWaveMin = 256;
 
 template <int NC, bool kReg, int kMaxQB, int kNT, int kOcc>
 hipError_t launch_screen_k(ScreenArgs a, int32_t grid, hipStream_t s) {
@@ -536,9 +544,10 @@ hipError_t launch_screen_k(ScreenArgs a, int32_t grid, hipStream_t s) {
         hipDeviceGetAttribute(&per_block, hipDeviceAttributeMaxSharedMemoryPerBlock, dev) !=
             hipSuccess)
       return (size_t)0;
-    const size_t left =
-        (size_t)per_block > fa.sharedSizeBytes ? (size_t)per_block - fa.sharedSizeBytes : 0;
-    return std::min(left, (size_t)kScreenDynLds) & ~(size_t)15;
+    // kOcc work-groups share a CU's 160 KB
+    const size_t most = std::min((size_t)per_block, (size_t)(160 * 1024 / kOcc));
+    const size_t left = most > fa.sharedSizeBytes ? most - fa.sharedSizeBytes : 0;
+    return std::min(left, (size_t)kScreenDynLds) & ~(size_t)1023;
   }();
   if (dyn_max == 0) return hipErrorInvalidValue;
   static const hipError_t attr =
@@ -548,10 +557,9 @@ hipError_t launch_screen_k(ScreenArgs a, int32_t grid, hipStream_t s) {
   if (a.tile_q > 16 * kMaxQB || a.tile_q < 1 || a.k < 1 || a.k > 64) return hipErrorInvalidValue;
   const size_t rows = (size_t)(a.tile_q + 15) / 16 * 16;
   const size_t stage = (rows * (4 * NC + 1) * 16 + 1023) & ~(size_t)1023;
-  const size_t share = kOcc == 1 ? dyn_max : std::min(dyn_max, (size_t)(64 * 1024));
-  const size_t room = share > stage ? share - stage : 0;
+  const size_t room = dyn_max > stage ? dyn_max - stage : 0;
   a.arena_lds = (int32_t)std::min<size_t>(room / sizeof(TileSpill), kArenaLdsMax);
-  if (a.arena_lds < 256 * (kNT / 64)) return hipErrorInvalidValue;
+  if (a.arena_lds < kArenaWaveMin * (kNT / 64)) return hipErrorInvalidValue;
   a.cand_u4 = (int32_t)(stage / 16);
   const size_t lds = stage + (size_t)a.arena_lds * sizeof(TileSpill);
   hipLaunchKernelGGL((screen_scan_kernel<NC, kReg, kMaxQB, kNT, kOcc>), dim3(grid), dim3(kNT), lds,

@@ -277,7 +277,7 @@ hipError_t launch_screen_queries(int dtype, int d, const void* queries, int64_t 
 // Largest query tile of the screened kernels, by round kind, and the launch
 // (dense: a.tile_q > screen_tile_q(d, false) where the two differ).
 int screen_tile_q(int d, bool dense);
-int screen_grid_per_cu(int d);
+int screen_grid_per_cu(int d, bool dense);
 hipError_t launch_screen_scan(const ScreenArgs& a, int32_t grid, hipStream_t s);
 hipError_t launch_screen_scan_reg(int nc, const ScreenArgs& a, int32_t grid, hipStream_t s);
 hipError_t launch_screen_scan_lds(int nc, const ScreenArgs& a, int32_t grid, hipStream_t s);
