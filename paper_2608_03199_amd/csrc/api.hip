@@ -616,7 +616,8 @@ int search_impl(sieve_index* ix, const void* queries, int64_t nq, const int64_t*
 
   RoundCounters* rc = (RoundCounters*)ix->rc.p;
   const int e = elem_bytes(ix->dtype);
-  const ScanArgs sa0 = make_scan_args(ix, queries, exclude, pl);
+  ScanArgs sa0 = make_scan_args(ix, queries, exclude, pl);
+  sa0.stats = timed ? 1 : 0;
 
   int pool_retries = 0;
   for (;;) {
@@ -844,7 +845,8 @@ int search_impl(sieve_index* ix, const void* queries, int64_t nq, const int64_t*
     HIP_TRY(launch_topk(nq, pl.k, (const Hit*)ix->pool_sorted.p, (const int64_t*)ix->hoff.p,
                         (const int32_t*)ix->hcount.p, probes_src, pl.n, out_map, out_ids,
                         out_scores, out_probes, cal ? cal->frank : nullptr,
-                        spec_used ? (const int32_t*)ix->state_a.p : nullptr, rc, s));
+                        spec_used ? (const int32_t*)ix->state_a.p : nullptr,
+                        timed ? rc : nullptr, s));
     const int f1 = mark(ix, timed, s);
     span(ix, kFinal, f0, f1);
     span(ix, kTotal, t_begin, f1);

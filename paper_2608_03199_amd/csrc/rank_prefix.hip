@@ -550,13 +550,13 @@ hipError_t launch_prefix_k(const void* queries, int64_t q0, int32_t nqc, const v
   return hipGetLastError();
 }
 
-// 768-dimension fp16 rows take the wide configuration: 96 queries per pass
-// of the centroids instead of 48.
+// fp16 rows of 384 dimensions and more take the wide configuration: 96
+// queries per pass of the centroids instead of 48 (768 dimensions) or 64.
 template <int DT, int D>
 hipError_t launch_prefix_t(const void* queries, int64_t q0, int32_t nqc, const void* centroids,
                            const void* cfrag, int32_t nlist, int32_t d, int32_t R, double cmax,
                            int32_t cap, unsigned long long* cand, int32_t* ccount, hipStream_t s) {
-  if constexpr (DT == SIEVE_F16 && D == 768)
+  if constexpr (DT == SIEVE_F16 && D >= 384)
     return launch_prefix_k<DT, D, kPrefixThreadsWide>(queries, q0, nqc, centroids, cfrag, nlist,
                                                       d, R, cmax, cap, cand, ccount, s);
   else
@@ -584,10 +584,12 @@ hipError_t launch_finish_t(const void* queries, int64_t q0, int32_t nqc, const v
 }  // namespace
 
 // The ranking kernels of compile-time dimensions (the register-query kernel
-// for fp16 128, the LDS-staged one for fp16 768 and fp32 64 / 128) read the
-// copy; the others read the row-major centroids.
+// for fp16 128, the LDS-staged one for the others) read the copy; the rest
+// read the row-major centroids.
 size_t centroid_frag_bytes(int dtype, int d, int32_t nlist) {
-  const bool fixed = dtype == SIEVE_F32 ? (d == 64 || d == 128) : (d == 128 || d == 768);
+  const bool fixed = dtype == SIEVE_F32 ? (d == 64 || d == 128)
+                                        : (d == 128 || d == 256 || d == 384 || d == 512 ||
+                                           d == 768);
   if (!fixed || nlist <= 0) return 0;
   const int64_t row_bytes = (int64_t)d * (dtype == SIEVE_F32 ? 4 : 2);
   return (size_t)((nlist + 15) / 16) * (size_t)((row_bytes + 63) / 64) * 1024;
@@ -644,9 +646,13 @@ hipError_t launch_rank_prefix(int dtype, const void* queries, int64_t q0, int32_
     e = d == 64 ? SIEVE_PREFIX(SIEVE_F32, 64)
                 : d == 128 ? SIEVE_PREFIX(SIEVE_F32, 128) : SIEVE_PREFIX(SIEVE_F32, 0);
   } else {
-    e = d == 128   ? SIEVE_PREFIX(SIEVE_F16, 128)
-        : d == 768 ? SIEVE_PREFIX(SIEVE_F16, 768)
-                   : SIEVE_PREFIX(SIEVE_F16, 0);
+    switch (d) {
+      case 256: e = SIEVE_PREFIX(SIEVE_F16, 256); break;
+      case 384: e = SIEVE_PREFIX(SIEVE_F16, 384); break;
+      case 512: e = SIEVE_PREFIX(SIEVE_F16, 512); break;
+      case 768: e = SIEVE_PREFIX(SIEVE_F16, 768); break;
+      default: e = SIEVE_PREFIX(SIEVE_F16, 0);
+    }
   }
 #undef SIEVE_PREFIX
   if (e != hipSuccess) return e;

@@ -350,6 +350,13 @@ __global__ void sched_tiles_kernel(int32_t* __restrict__ cnt, const int32_t* __r
   }
 }
 
+__device__ __forceinline__ unsigned long long screened_sum(const RoundCounters* rc) {
+  unsigned long long sum = 0;
+#pragma unroll
+  for (int x = 0; x < 8; ++x) sum += rc->screened[x];
+  return sum;
+}
+
 // The round's summary for the host: one wave reads the counters (the
 // update launch before it on the stream has finished) and writes them to
 // coherent pinned host memory with system-scope stores.
@@ -364,7 +371,8 @@ __global__ void publish_round_kernel(const RoundCounters* __restrict__ rc,
   __hip_atomic_store(&out->sched_error, rc->sched_error, __ATOMIC_RELAXED,
                      __HIP_MEMORY_SCOPE_SYSTEM);
   __hip_atomic_store(&out->hits, rc->hits, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
-  __hip_atomic_store(&out->screened, rc->screened, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+  __hip_atomic_store(&out->screened, screened_sum(rc), __ATOMIC_RELAXED,
+                     __HIP_MEMORY_SCOPE_SYSTEM);
   __hip_atomic_store(&out->item_rows, rc->item_rows, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
   __threadfence_system();
 }
@@ -391,7 +399,8 @@ __device__ __forceinline__ void publish_from_last(RoundCounters* rc, RoundSummar
   __hip_atomic_store(&out->sched_error, rc->sched_error, __ATOMIC_RELAXED,
                      __HIP_MEMORY_SCOPE_SYSTEM);
   __hip_atomic_store(&out->hits, rc->hits, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
-  __hip_atomic_store(&out->screened, rc->screened, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+  __hip_atomic_store(&out->screened, screened_sum(rc), __ATOMIC_RELAXED,
+                     __HIP_MEMORY_SCOPE_SYSTEM);
   __hip_atomic_store(&out->item_rows, rc->item_rows, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
   __threadfence_system();
 }
@@ -490,19 +499,29 @@ __global__ void update_lookahead_kernel(int64_t nq, const int32_t* __restrict__ 
     lookahead_one(q, P, n, W, stop, lmax, have, ext, items, item_cap, cnt, rc, hitbits, words, issued,
                   spec_max, spec_min, &e0, &ne);
   // The new items of the committed path: one claim on the item counter per
-  // wave (a one-address atomic per query would serialise the first round's
-  // updates), each lane's share at its prefix of the wave's claim.
-  const int lane = threadIdx.x & 63;
+  // work-group (claims on one address serialise, at about 0.16 us each: a
+  // claim per wave took 10 of the 14 us of 4,000 queries' update, UPD_US now),
+  // each lane's share at its prefix of the claim.
+  __shared__ int s_tot[kThreads / 64], s_base;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   int inc = ne;
 #pragma unroll
   for (int o = 1; o < 64; o <<= 1) {
     const int t = __shfl_up(inc, o);
     if (lane >= o) inc += t;
   }
-  const int total = __shfl(inc, 63);
-  int wbase = 0;
-  if (lane == 63 && total > 0) wbase = atomicAdd(&rc->new_items, total);
-  wbase = __shfl(wbase, 63);
+  if (lane == 63) s_tot[wave] = inc;
+  __syncthreads();
+  int wbase = 0, total = 0;
+#pragma unroll
+  for (int w = 0; w < kThreads / 64; ++w) {
+    const int t = s_tot[w];
+    wbase += w < wave ? t : 0;
+    total += t;
+  }
+  if (threadIdx.x == 0) s_base = total > 0 ? atomicAdd(&rc->new_items, total) : 0;
+  __syncthreads();
+  wbase += s_base;
   // eight ranks' lists are loaded at a time (one by one, each load's latency
   // shows: W = 8 new ranks a query took 14 us, now 9)
   const int base = wbase + inc - ne;

@@ -234,10 +234,13 @@ __device__ __forceinline__ int rescore_pairs(TileSpill* ent, int n, const Screen
     }
     f32x4 acc[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
     int c = 0;
-    for (; c + 4 <= full; c += 4) {
-      u32x4 qv[4][2], rv[4][2];
+    // U chunks of both groups are in flight at once: each step is one trip to
+    // memory, so long rows take eight chunks a step
+    auto chunks = [&](auto uc) {
+      constexpr int U = decltype(uc)::value;
+      u32x4 qv[U][2], rv[U][2];
 #pragma unroll
-      for (int u = 0; u < 4; ++u) {
+      for (int u = 0; u < U; ++u) {
 #pragma unroll
         for (int g = 0; g < 2; ++g) {
           qv[u][g] = qp[g][4 * (c + u) + h];
@@ -245,11 +248,14 @@ __device__ __forceinline__ int rescore_pairs(TileSpill* ent, int n, const Screen
         }
       }
 #pragma unroll
-      for (int u = 0; u < 4; ++u) {
+      for (int u = 0; u < U; ++u) {
 #pragma unroll
         for (int g = 0; g < 2; ++g) acc[g] = mma_chunk<DT>(qv[u][g], rv[u][g], acc[g]);
       }
-    }
+      c += U;
+    };
+    while (c + 8 <= full) chunks(std::integral_constant<int, 8>{});
+    while (c + 4 <= full) chunks(std::integral_constant<int, 4>{});
     for (; c < full + (rem ? 1 : 0); ++c) {
       const bool ok = 4 * c + h < dsegs;
       const int sc = ok ? 4 * c + h : 0;
@@ -332,6 +338,7 @@ __global__ __launch_bounds__(kNT, kOcc) void screen_scan_kernel(ScreenArgs a) {
   __shared__ __align__(16) int32_t s_init[2][kTQ];  // accumulator start: -T of the query
   __shared__ TileShared<kTQ, kNT> S;
   __shared__ int s_first[3], s_next;
+  __shared__ unsigned long long s_passed[kNT / 64];
   TileSpill* const arena_g = a.spill + (size_t)blockIdx.x * arena_block_entries(a.spill_cap);
   SrtEnt* const arena_srt = (SrtEnt*)(arena_g + a.spill_cap);
   TileSpill* const s_arena = (TileSpill*)(lds + a.cand_u4);
@@ -524,7 +531,14 @@ __global__ __launch_bounds__(kNT, kOcc) void screen_scan_kernel(ScreenArgs a) {
     recN = recA;
     set = nset;
   }
-  if (lane == 0 && passed) atomicAdd(&a.rc->screened, passed);
+  // one add per work-group, spread over the XCDs
+  if (lane == 0) s_passed[wv] = passed;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    unsigned long long sum = 0;
+    for (int w = 0; w < nwv; ++w) sum += s_passed[w];
+    if (sum) atomicAdd(&a.rc->screened[home], sum);
+  }
 }
 
 // Dynamic LDS: the staged queries, then the arena (at least kArenaWaveMin

@@ -84,7 +84,8 @@ struct RoundCounters {
   unsigned long long cands;       // qualifying (query, row) pairs the scans found (whole search)
   int32_t heavy;                  // HeavyRec records claimed (whole search)
   int32_t sched_error;            // set when a round's tiles exceed the tile buffer
-  unsigned long long screened;    // pairs a screened scan scored exactly (whole search)
+  unsigned long long screened[8]; // pairs the screened scans scored exactly, by XCD (whole
+                                  // search); one address for all work-groups would serialise
   // Sums of out_probes and of the qualifying candidates merged by the final
   // top-k, spread over kStatSlots counters (work-group b adds to slot
   // b % kStatSlots): thousands of adds to one address would serialise.
@@ -201,6 +202,7 @@ struct ScanArgs {
   uint32_t* hitbits = nullptr;
   int32_t hit_words = 0;       // 32-bit words per query in hitbits
   float tau;
+  int32_t stats = 0;           // 1: count the qualifying pairs (timed searches)
 };
 
 struct ScreenArgs : ScanArgs {
@@ -400,6 +402,7 @@ hipError_t launch_topk(int64_t nq, int32_t k, const Hit* sorted, const int64_t* 
                        const int32_t* out_map, int64_t* out_ids, float* out_scores,
                        int32_t* out_probes, int32_t* out_rank, const int32_t* rank_limit,
                        RoundCounters* rc, hipStream_t s);
+// (rc: null, or where the probe and candidate sums go)
 // Best k of nshard per-index top-k lists per query ([nshard][nq][k], id -1
 // padding) and the sum of the per-index probe counts ([nshard][nq]).
 hipError_t launch_merge_shards(int64_t nq, int32_t k, int32_t nshard, const int64_t* sids,

@@ -132,8 +132,10 @@ __device__ __forceinline__ void finish_tile(const ScanArgs& a, TileShared<kTQ, k
     }
     c += lost;
   }
-  {
-    // qualifying pairs of the tile, for the statistics: one add per wave
+  if (a.stats) {
+    // qualifying pairs of the tile, for the statistics: one add per wave.
+    // Not counted where none are asked for: adds on one address serialise
+    // (30,000 items over 1,024 lists: 11 of 78 us a round).
     unsigned long long cs = (unsigned long long)c;
     for (int o = 32; o > 0; o >>= 1) cs += __shfl_xor(cs, o);
     if (lane == 0 && cs) atomicAdd(&a.rc->cands, cs);

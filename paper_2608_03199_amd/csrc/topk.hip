@@ -149,6 +149,9 @@ __global__ __launch_bounds__(256) void topk_kernel(int64_t nq, int32_t k,
     probes += (unsigned long long)p;
     cands += (unsigned long long)m;
   }
+  // the sums only serve the statistics: thousands of adds on a few addresses
+  // (10,000 queries: 10 of 19 us) are left out where none are asked for
+  if (!rc) return;
   if (lane == 0) {
     s_probes[wave] = probes;
     s_cands[wave] = cands;
