@@ -32,6 +32,7 @@ ROOT = os.path.dirname(os.path.abspath(__file__))
 sys.path.insert(0, ROOT)
 
 HBM_PEAK_GBS = 8000.0
+INT8_PEAK_TOPS = 5000.0
 MFMA_PEAK_TFLOPS = {"f32": 157.3, "f16": 2500.0}
 PMC_FILE = os.path.join(ROOT, "profiles", "scan_traffic_pmc.json")
 CONFIG_ORDER = ["c1", "c2", "c3", "c5"]
@@ -40,7 +41,9 @@ ORACLE_ONE_THREAD = {"tiny": 150, "tiny16": 150, "c1": 1000, "c2": 4000, "c3": 1
 # parity subset, checked with the threaded oracle (all queries of the small workloads)
 ORACLE_PARITY = {"tiny": 150, "tiny16": 150, "c1": 1000, "c2": 10000, "c3": 5000, "c5": 5000}
 ORACLE_MAX_THREADS = 16
-SCAN_SOURCES = ["paper_2608_03199_amd/csrc/scan.hip", "paper_2608_03199_amd/csrc/mfma_tile.h"]
+SCAN_SOURCES = ["paper_2608_03199_amd/csrc/" + f for f in (
+    "scan.hip", "mfma_tile.h", "tile_end.h", "screen_tile.h", "screen_scan_reg.hip",
+    "screen_scan_lds.hip")]
 
 
 def log(*a):
@@ -75,20 +78,24 @@ def workload_name(spec) -> str:
             f"nprobe_max={spec.nprobe_max}, Algorithm 2 lookahead")
 
 
-def roofline(dtype, rounds, config):
+def roofline(spec, rounds, config):
     """Roofline of the partition scan over the timed steps' rounds.
 
     Step-aggregate form (`frac`): the summed algorithmic bytes and flops of a step priced
     against the bound they imply, achieved = per-launch work / average launch time.
     Per-round form (`frac_rounds`): sum over rounds of max(B_r / BW, F_r / P) divided by
     the summed measured scan time, each round against its own bound."""
-    peak_f = MFMA_PEAK_TFLOPS[dtype]
+    # a screened round multiplies 8-bit rows: its products' peak is the 8-bit one
+    row = spec.d * (4 if spec.dtype == "f32" else 2)
+    peaks = [INT8_PEAK_TOPS if r["scan_bytes"] < 0.9 * row * r["list_rows"]
+             else MFMA_PEAK_TFLOPS[spec.dtype] for r in rounds]
+    peak_f = max(peaks, default=MFMA_PEAK_TFLOPS[spec.dtype])
     launches = len(rounds)
     B = sum(r["scan_bytes"] for r in rounds)
     F = sum(r["scan_flops"] for r in rounds)
     T = sum(r["ms_scan"] for r in rounds) * 1e-3
     t_hbm = B / (HBM_PEAK_GBS * 1e9)
-    t_mfma = F / (peak_f * 1e12)
+    t_mfma = sum(r["scan_flops"] / (p * 1e12) for r, p in zip(rounds, peaks))
     bound = "hbm" if t_hbm >= t_mfma else "mfma"
     avg_s = T / max(launches, 1)
     gbs = (B / max(launches, 1)) / avg_s / 1e9 if avg_s > 0 else 0.0
@@ -100,7 +107,7 @@ def roofline(dtype, rounds, config):
         roof = {"bound": "mfma", "achieved": round(tfs, 2), "peak": peak_f, "unit": "TFLOP/s",
                 "frac": round(tfs / peak_f, 4)}
     roof["traffic"] = measured_traffic(config)
-    roof["kernel"] = "scan_kernel (partition scan + tau test)"
+    roof["kernel"] = "screen_scan_kernel / scan_kernel (partition scan + tau test)"
     roof["launches_per_step"] = launches
     roof["avg_launch_ms"] = round(avg_s * 1e3, 5)
     roof["alg_bytes_per_launch"] = round(B / max(launches, 1))
@@ -108,9 +115,9 @@ def roofline(dtype, rounds, config):
     roof["other_bound_frac"] = round((tfs / peak_f) if bound == "hbm" else (gbs / HBM_PEAK_GBS),
                                      4)
     per, tstar_sum = [], 0.0
-    for r in rounds:
+    for r, p in zip(rounds, peaks):
         tb = r["scan_bytes"] / (HBM_PEAK_GBS * 1e9)
-        tf = r["scan_flops"] / (peak_f * 1e12)
+        tf = r["scan_flops"] / (p * 1e12)
         ts = max(tb, tf)
         tstar_sum += ts
         t = r["ms_scan"] * 1e-3
@@ -202,7 +209,7 @@ def run_config(name, args, ps, sw, np, torch, dev, headline):
            "partition_vectors_per_s": round(stats.vectors_scanned * K / t_sieve, 1),
            "candidates": int(stats.hits), "pool_entries": int(stats.pool_entries),
            "heavy_records": int(stats.heavy_records)}
-    roof = roofline(spec.dtype, rounds, name)
+    roof = roofline(spec, rounds, name)
     # per-step round table: the last step's rounds (every step runs the same rounds)
     roof["rounds"] = roof["rounds"][-stats.rounds:] if stats.rounds else []
     res["scan_hbm_gbs"] = round(sum(x["scan_bytes"] for x in rounds) /
@@ -242,7 +249,7 @@ def run_config(name, args, ps, sw, np, torch, dev, headline):
     res["fixed_phase_ms"] = {k: round(getattr(fst, "ms_" + k), 4) for k in
                              ("rank", "sched", "scan", "finalize", "total")}
     res["fixed_roofline"] = {k: v for k, v in roofline(
-        spec.dtype, [x.as_dict() for x in ix.round_log()], name).items()
+        spec, [x.as_dict() for x in ix.round_log()], name).items()
         if k not in ("rounds", "traffic")}
 
     # in-call calibration (Appendix A): a seeded 2% sample fully probed, the window chosen

@@ -105,7 +105,8 @@ typedef struct sieve_stats {
   int64_t hits;             /* qualifying (query, row) pairs found (searched ranks past the
                                final stop line included)                                  */
   double scan_bytes;        /* algorithmic bytes of the scan: list rows + per-item query
-                               rows and item records + candidate records written          */
+                               rows (8-bit rows in a screened round) and item records +
+                               candidate records written                                  */
   double scan_flops;        /* 2 * d * vectors_scanned                                     */
   double rank_flops;        /* 2 * d * nq * nlist (the centroid screen)                    */
   float ms_rank, ms_sched, ms_scan, ms_update, ms_finalize, ms_total; /* device time, ms */
@@ -302,7 +303,8 @@ typedef struct sieve_round {
   int64_t item_rows;   /* sum over the items of their list's rows (rows scored)         */
   int64_t list_loads;  /* distinct non-empty lists touched                              */
   int64_t candidates;  /* candidate records the scan wrote                              */
-  double scan_bytes;   /* list rows + per-item query rows and records + candidates, B   */
+  double scan_bytes;   /* list rows + per-item query rows and records + candidates, B   
+                          (a screened round's rows are the 8-bit ones)                  */
   double scan_flops;   /* 2 * d * item_rows                                             */
   float ms_scan;       /* device time of the round's scan launch (HIP events)           */
   int32_t kind;        /* 0: threshold-search round, 1: fixed-probe chunk               */

@@ -137,6 +137,7 @@ struct sieve_index {
   // round as it runs, the finished records after the final synchronisation
   std::vector<int64_t> round_items;
   std::vector<int> round_span;
+  std::vector<double> round_row_bytes;  // bytes of a row in the copy the round's scan reads
   std::vector<sieve_round> rounds_log;
   int32_t rounds_logged = 0;  // rounds of that search (records past kMaxLogRounds are dropped)
 };
@@ -203,6 +204,7 @@ void reset_timeline(sieve_index* ix) {
   ix->span_b.clear();
   ix->round_items.clear();
   ix->round_span.clear();
+  ix->round_row_bytes.clear();
 }
 
 // After the stream has drained: milliseconds per phase, and scan span count.
@@ -546,6 +548,8 @@ int run_round(sieve_index* ix, const ScanArgs& sa, int n_items, int64_t q0, cons
     // the round's counters, for the per-round log (sieve_round_log)
     const int slot = (int)ix->round_items.size();
     ix->round_items.push_back(n_items);
+    ix->round_row_bytes.push_back(pl.screen ? 64.0 * screen_chunks(ix->d)
+                                            : (double)ix->d * elem_bytes(ix->dtype));
     ix->round_span.push_back(e1 >= 0 && e2 >= 0 ? (int)ix->span_phase.size() - 1 : -1);
     if (slot < kMaxLogRounds)
       HIP_TRY(launch_snapshot_round(rc, (RoundSnap*)ix->rlog.p + slot, 0, s));
@@ -563,7 +567,6 @@ int finish_round_log(sieve_index* ix, int32_t kind, hipStream_t s) {
                            hipMemcpyDeviceToHost, s));
     HIP_TRY(hipStreamSynchronize(s));
   }
-  const double eb = (double)ix->d * elem_bytes(ix->dtype);
   ix->rounds_log.assign((size_t)n, sieve_round{});
   ix->rounds_logged = (int32_t)ix->round_items.size();
   RoundSnap prev = {0, 0, 0, 0};
@@ -574,6 +577,7 @@ int finish_round_log(sieve_index* ix, int32_t kind, hipStream_t s) {
     o.item_rows = (int64_t)(snap[r].item_rows - prev.item_rows);
     o.list_loads = (int64_t)(snap[r].list_loads - prev.list_loads);
     o.candidates = (int64_t)(snap[r].cands - prev.cands);
+    const double eb = ix->round_row_bytes[(size_t)r];
     o.scan_bytes = (double)o.list_rows * eb + (double)o.items * (eb + sizeof(Item)) +
                    (double)o.candidates * sizeof(Hit);
     o.scan_flops = 2.0 * (double)ix->d * (double)o.item_rows;
@@ -877,8 +881,12 @@ int search_impl(sieve_index* ix, const void* queries, int64_t nq, const int64_t*
       stats->hits = (int64_t)h.cands;
       stats->pool_entries = (int64_t)cand_sum;
       stats->heavy_records = (int64_t)h.heavy;
-      stats->scan_bytes = (double)h.list_rows * eb + (double)items_total * (eb + sizeof(Item)) +
-                          (double)cand_sum * sizeof(Hit);
+      // rounds past the log count as exact scans
+      double bytes = (double)h.list_rows * eb + (double)items_total * (eb + sizeof(Item));
+      for (size_t r = 0; r < ix->rounds_log.size(); ++r)
+        bytes -= (eb - ix->round_row_bytes[r]) *
+                 (double)(ix->rounds_log[r].list_rows + ix->rounds_log[r].items);
+      stats->scan_bytes = bytes + (double)cand_sum * sizeof(Hit);
       stats->scan_flops = 2.0 * (double)ix->d * (double)h.item_rows;
       stats->rank_flops = 2.0 * (double)ix->d * (double)nq * (double)ix->nlist;
       stats->ms_rank = ms[kRank];

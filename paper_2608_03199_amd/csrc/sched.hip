@@ -500,7 +500,7 @@ __global__ void update_lookahead_kernel(int64_t nq, const int32_t* __restrict__ 
                   spec_max, spec_min, &e0, &ne);
   // The new items of the committed path: one claim on the item counter per
   // work-group (claims on one address serialise, at about 0.16 us each: a
-  // claim per wave took 10 of the 14 us of 4,000 queries' update, UPD_US now),
+  // claim per wave took 10 of the 14 us of 4,000 queries' update, 9 now),
   // each lane's share at its prefix of the claim.
   __shared__ int s_tot[kThreads / 64], s_base;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -523,7 +523,7 @@ __global__ void update_lookahead_kernel(int64_t nq, const int32_t* __restrict__ 
   __syncthreads();
   wbase += s_base;
   // eight ranks' lists are loaded at a time (one by one, each load's latency
-  // shows: W = 8 new ranks a query took 14 us, now 9)
+  // shows: W = 8 new ranks a query)
   const int base = wbase + inc - ne;
   for (int j0 = 0; __ballot(j0 < ne) != 0ull; j0 += 8) {
     int p[8];
