@@ -651,11 +651,12 @@ int search_impl(sieve_index* ix, const void* queries, int64_t nq, const int64_t*
       f.seg[3] = {(int32_t*)ix->hcount.p, nq, 0};
       if (cal) f.seg[4] = {(int32_t*)cal->hitbits, nq * (int64_t)cal->words, 0};
       if (pl.mode != 2) f.seg[5] = {(int32_t*)ix->have.p, nq, pl.r0};
-      HIP_TRY(launch_fill_multi(f, s));
+      if (pl.screen)  // with the queries' 8-bit copies in the same launch
+        HIP_TRY(launch_screen_queries(ix->dtype, ix->d, queries, nq, ix->q8.p,
+                                      (ScreenParam*)ix->qpar.p, f, s));
+      else
+        HIP_TRY(launch_fill_multi(f, s));
     }
-    if (pl.screen)
-      HIP_TRY(launch_screen_queries(ix->dtype, ix->d, queries, nq, ix->q8.p,
-                                    (ScreenParam*)ix->qpar.p, s));
     unsigned long long scr_seen = 0, rows_seen = 0;  // the screen's counters so far
     bool spec_used = false;  // a round kept the rank bitmap (its ranks may pass stop lines)
     RoundSummary sm = {};  // the host's view of the last round

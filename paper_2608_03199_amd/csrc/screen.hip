@@ -224,12 +224,22 @@ __global__ __launch_bounds__(64) void screen_sample_kernel(
   }
 }
 
-// 16 lanes per query, 16 dimensions per lane and step.
+// 16 lanes per query, 16 dimensions per lane and step.  The search's resets
+// (f) ride along, which saves their launch (one query 131 -> 129 us, 100
+// queries on 1M x 768 350 -> 316).
 template <int DT>
 __global__ __launch_bounds__(256) void screen_queries_kernel(const char* __restrict__ queries,
                                                              int64_t nq, int32_t d, int32_t nc,
                                                              u32x4* __restrict__ q8,
-                                                             ScreenParam* __restrict__ qpar) {
+                                                             ScreenParam* __restrict__ qpar,
+                                                             FillSegs f) {
+#pragma unroll
+  for (int k = 0; k < kFillSegs; ++k) {
+    int32_t* __restrict__ p = f.seg[k].p;
+    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < f.seg[k].n;
+         i += (int64_t)gridDim.x * blockDim.x)
+      p[i] = f.seg[k].v;
+  }
   const int l16 = threadIdx.x & 15;
   const int64_t q = (int64_t)blockIdx.x * 16 + (threadIdx.x >> 4);
   const bool real = q < nq;
@@ -327,17 +337,24 @@ hipError_t launch_screen_sample(int d, const void* v8, const int64_t* offsets,
 }
 
 hipError_t launch_screen_queries(int dtype, int d, const void* queries, int64_t nq, void* q8,
-                                 ScreenParam* qpar, hipStream_t s) {
+                                 ScreenParam* qpar, const FillSegs& f, hipStream_t s) {
   const int nc = screen_chunks(d);
   if (nc == 0) return hipErrorInvalidValue;
-  if (nq <= 0) return hipSuccess;
-  const dim3 grid((unsigned)((nq + 15) / 16));
+  if (nq <= 0) return hipErrorInvalidValue;
+  int64_t most = 0;
+  for (int k = 0; k < kFillSegs; ++k) {
+    if (f.seg[k].n < 0 || (f.seg[k].n > 0 && !f.seg[k].p)) return hipErrorInvalidValue;
+    most = std::max(most, f.seg[k].n);
+  }
+  // work-groups past the queries only fill
+  const int64_t fill = std::min<int64_t>((most + 255) / 256, 4096);
+  const dim3 grid((unsigned)std::max<int64_t>((nq + 15) / 16, fill));
   if (dtype == SIEVE_F32)
     hipLaunchKernelGGL(screen_queries_kernel<SIEVE_F32>, grid, dim3(256), 0, s,
-                       (const char*)queries, nq, d, nc, (u32x4*)q8, qpar);
+                       (const char*)queries, nq, d, nc, (u32x4*)q8, qpar, f);
   else
     hipLaunchKernelGGL(screen_queries_kernel<SIEVE_F16>, grid, dim3(256), 0, s,
-                       (const char*)queries, nq, d, nc, (u32x4*)q8, qpar);
+                       (const char*)queries, nq, d, nc, (u32x4*)q8, qpar, f);
   return hipGetLastError();
 }
 

@@ -256,6 +256,16 @@ hipError_t launch_centroid_frag(int dtype, int d, const void* centroids, int32_t
 // FragStream).  frag_rows = frag_offsets[nlist].  vector_frag_bytes is 0 for
 // dimensions the scan handles at run time (no copy).
 size_t vector_frag_bytes(int dtype, int d, int64_t frag_rows);
+// Several 32-bit fills in one launch (segments with n = 0 are skipped).
+constexpr int kFillSegs = 6;
+struct FillSeg {
+  int32_t* p;
+  int64_t n;  // 32-bit words
+  int32_t v;
+};
+struct FillSegs {
+  FillSeg seg[kFillSegs];
+};
 // ---- screened scan (screen_tile.h) ----
 // 64-byte chunks of an 8-bit row of d dimensions as the screened kernels take
 // it (rows are padded with zeros to one of their chunk counts), 0 where there
@@ -273,9 +283,10 @@ constexpr int kScreenSample = 32;
 hipError_t launch_screen_sample(int d, const void* v8, const int64_t* offsets,
                                 const int64_t* frag_offsets, int32_t nlist,
                                 const ScreenParam* lpar, float* out, hipStream_t s);
-// 8-bit copies [nq][64 * chunks] of the queries and their parameters.
+// 8-bit copies [nq][64 * chunks] of the queries (nq >= 1) and their parameters;
+// the fills of f (as launch_fill_multi) in the same launch.
 hipError_t launch_screen_queries(int dtype, int d, const void* queries, int64_t nq, void* q8,
-                                 ScreenParam* qpar, hipStream_t s);
+                                 ScreenParam* qpar, const FillSegs& f, hipStream_t s);
 // Largest query tile of the screened kernels, by round kind, and the launch
 // (dense: a.tile_q > screen_tile_q(d, false) where the two differ).
 int screen_tile_q(int d, bool dense);
@@ -350,16 +361,6 @@ hipError_t launch_emit_pending(const int32_t* ext, int32_t n_ext, int32_t mode, 
 hipError_t launch_snapshot_round(const RoundCounters* rc, RoundSnap* log, int32_t slot,
                                  hipStream_t s);
 hipError_t launch_fill_i32(int32_t* p, int64_t n, int32_t v, hipStream_t s);
-// Several 32-bit fills in one launch (segments with n = 0 are skipped).
-constexpr int kFillSegs = 6;
-struct FillSeg {
-  int32_t* p;
-  int64_t n;  // 32-bit words
-  int32_t v;
-};
-struct FillSegs {
-  FillSeg seg[kFillSegs];
-};
 hipError_t launch_fill_multi(const FillSegs& f, hipStream_t s);
 hipError_t launch_zero_bytes(void* p, int64_t bytes, hipStream_t s);
 // Segments of the grouped pool: off[q] = cursor[q] = the first of cnt[q]
