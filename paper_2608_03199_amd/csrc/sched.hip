@@ -240,11 +240,13 @@ __global__ __launch_bounds__(kOffThreads) void sched_offsets_kernel(
 // bound that is not a number, or norms whose product could overflow fp32 on
 // the way to a score, give -2^28 (every pair is scored).
 constexpr double kThrLim = 268435456.0;
+constexpr double kScoreUnderflow = 1.1754943508222875e-38;  // 2^-126
 __device__ __forceinline__ int32_t screen_threshold(const ScreenParam& q, const ScreenParam& l,
                                                     float tau, int32_t d) {
   const double nq = (double)q.norm + (double)q.err;  // >= |q|
   const double slack = (double)q.norm * l.err + (double)q.err * l.norm +
-                       2.0 * (double)(d + 2) * 5.9604644775390625e-08 * nq * l.norm;
+                       2.0 * (double)(d + 2) * 5.9604644775390625e-08 * nq * l.norm +
+                       kScoreUnderflow * (double)d * (2.0 + nq + l.norm);
   const double t = ((double)tau - slack) / ((double)q.s * (double)l.s);
   if (!(nq * l.norm < 1e37)) return -(int32_t)kThrLim;
   if (!(t > -kThrLim)) return -(int32_t)kThrLim;

@@ -9,10 +9,16 @@
 // with e_l the largest |x - x^| and n_l the largest |x| of the list (both
 // rounded up, as are |q^| and |q - q^|).  The integer product is exact.  The
 // scan's score is the fp32 sum of the products, at most
-// 2 (d + 2) 2^-24 |q| |x| above q.x.  So a pair whose score reaches tau has
+//   2 (d + 2) 2^-24 |q| |x| + u,  u = 2^-126 d (2 + |q| + |x|),
+// above q.x.  The first term is the rounding of d products and sums; u is
+// what underflow adds to it, which no relative term covers: a product or a
+// sum below 2^-126 may lose all of itself (2 d 2^-126), and so may a stored
+// value below it (|q_t| or |x_t| times 2^-126 each; the matrix units were
+// measured to keep denormal values, the bound does not need them to).  So a
+// pair whose score reaches tau has
 //   qi.xi >= T(q, l) = floor((tau - slack) / (s_q s_l)),
-// slack = |q^| e_l + |q - q^| n_l + 2 (d + 2) 2^-24 |q| n_l: no such pair is
-// screened out.  Pairs that pass are scored with the exact scan's MFMA
+// slack = |q^| e_l + |q - q^| n_l + 2 (d + 2) 2^-24 |q| n_l + u: no such pair
+// is screened out.  Pairs that pass are scored with the exact scan's MFMA
 // sequence on the stored values (the same bits) and compared with tau.  Where
 // the bound is not finite (a list or a query with inf or NaN, an overflowing
 // norm) T is below every product: all its pairs are scored.

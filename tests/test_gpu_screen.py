@@ -116,3 +116,14 @@ def test_screen_unusual_values(edit, dtype, tau):
     ix, v, ids = _index(96, torch.float32 if dtype == "f32" else torch.float16, 5, edit)
     sel = torch.arange(0, len(v), 7).cuda()
     _check(ix, v[sel].contiguous(), ids[sel].contiguous(), 5, tau)
+
+
+# Norms whose products leave fp32: a pair with a small negative product scores 0 (or -0) and
+# reaches tau = 0, whatever its integer product says.
+@pytest.mark.parametrize("scale", [1e-24, 1e-21, 1e-19])
+def test_screen_underflowing_products(scale):
+    ix, v, ids = _index(96, torch.float32, 5, lambda x: x * scale)
+    sel = torch.arange(0, len(v), 11).cuda()
+    q = torch.cat([v[sel], -v[sel], v[sel].flip(1)]).contiguous()
+    _check(ix, q, ids[sel].repeat(3).contiguous(), 5, 0.0)
+    _check(ix, q, ids[sel].repeat(3).contiguous(), 64, scale * scale / 2)
