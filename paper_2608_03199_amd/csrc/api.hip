@@ -301,6 +301,7 @@ struct SearchPlan {
   int spec_min;        // a line must move at least this far to speculate
   int hit_words;       // 32-bit words per query of the rank bitmap (spec)
   bool screen;         // screened scans (screen_tile.h)
+  bool screen_forced;  // in every round, however many pairs pass (SIEVE_SCREEN = 2)
   int s_chunk;         // rows per tile in their sparse rounds
   int s_chunk_dense;   // and in their dense rounds
 };
@@ -707,7 +708,7 @@ int search_impl(sieve_index* ix, const void* queries, int64_t nq, const int64_t*
         sm.rank_error = rs->rank_error;
         sm.heavy = rs->heavy;
         sm.hits = rs->hits;
-        if (pl.screen) {
+        if (pl.screen && !pl.screen_forced) {
           // the screen pays while few pairs pass it: a pair scored exactly
           // costs about 16 pairs of the exact scan's tiles (one pair of a
           // 16 x 16 product block is used)
@@ -947,10 +948,11 @@ int plan_search(const sieve_index* ix, int64_t nq, int32_t k, float tau, int32_t
   // pairs of one list whose score is within the slack of tau or above (a
   // query's first lists are the likes of its own).  The first round is checked
   // against the same limit as it runs.  SIEVE_SCREEN = 0 turns them off, 2
-  // forces them where the copy exists (tests).
+  // forces them in every round where the copy exists (tests).
   const int scr = env_count("SIEVE_SCREEN", 1);
   pl->screen = ix->v8 && scr != 0 && arena_on(ix);
-  if (pl->screen && scr != 2) {
+  pl->screen_forced = scr == 2;
+  if (pl->screen && !pl->screen_forced) {
     const auto& v = ix->scr_scores;
     const float lim = (float)((double)tau - ix->scr_slack);
     const size_t pass = (size_t)(v.end() - std::lower_bound(v.begin(), v.end(), lim));

@@ -1,7 +1,8 @@
 """The screened scan (8-bit bound, exact scores of what passes) against the exact scan.
 
-SIEVE_SCREEN=2 takes every scan through the screen, 0 none.  Both score a pair with the same
-MFMA sequence, so ids, probe counts and scores agree bit for bit (no tolerance)."""
+SIEVE_SCREEN=2 takes every scan through the screen, 0 none; the round log shows which copy
+each round read.  Both score a pair with the same MFMA sequence, so ids, probe counts and
+scores agree bit for bit (no tolerance)."""
 import contextlib
 import os
 
@@ -50,22 +51,44 @@ def _index(d, dtype, seed, edit=None):
 
 def _calls(ix, q, ex, k, tau):
     n = len(SIZES)
-    yield "search", lambda: ix.search(q, ex, k, tau, 2, n)
-    yield "basic", lambda: ix.search(q, ex, k, tau, 2, n, lookahead=False)
-    yield "speculative", lambda: ix.search(q, ex, k, tau, 2, n, speculative=True)
-    yield "fixed", lambda: ix.search_fixed(q, ex, k, tau, n)
+    yield "search", lambda **s: ix.search(q, ex, k, tau, 2, n, **s)
+    yield "basic", lambda **s: ix.search(q, ex, k, tau, 2, n, lookahead=False, **s)
+    yield "speculative", lambda **s: ix.search(q, ex, k, tau, 2, n, speculative=True, **s)
+    yield "fixed", lambda **s: ix.search_fixed(q, ex, k, tau, n, **s)
+
+
+def _same(a, b, name=""):
+    for x, y in zip(a, b):
+        assert torch.equal(x.view(torch.int32) if x.dtype == torch.float32 else x,
+                           y.view(torch.int32) if y.dtype == torch.float32 else y), name
+
+
+def _screened(ix):
+    """For each round of the last call with statistics, whether it read the 8-bit rows: a
+    round's bytes are list_rows rows, and per item one row and an 8-byte record, and 16 bytes
+    per candidate."""
+    out = []
+    for r in ix.round_log():
+        row = (r.scan_bytes - 8 * r.items - 16 * r.candidates) / (r.list_rows + r.items)
+        exact = ix.d * (2 if ix.dtype == torch.float16 else 4)
+        out.append(row != exact)
+        assert row == exact or row in [64 * c for c in (1, 2, 3, 4, 6, 8, 12, 16)]
+    return out
 
 
 def _check(ix, q, ex, k, tau, **env):
     for name, call in _calls(ix, q, ex, k, tau):
         with knobs(SIEVE_SCREEN=0, **env):
             a = call()
+            call(with_stats=True)
+        assert not any(_screened(ix)), name
         with knobs(SIEVE_SCREEN=2, **env):
             b = call()
+            c = call(with_stats=True)
+        assert all(x == (ix.d <= 1024) for x in _screened(ix)), name
         torch.cuda.synchronize()
-        for x, y in zip(a, b):
-            assert torch.equal(x.view(torch.int32) if x.dtype == torch.float32 else x,
-                               y.view(torch.int32) if y.dtype == torch.float32 else y), name
+        _same(a, b, name)
+        _same(a, c, name)
 
 
 # chunk edges of the 8-bit rows (64 dimensions), each compiled chunk count, partial 16- and
