@@ -295,6 +295,7 @@ struct SearchPlan {
   bool wide_rank;      // rank with room for every boundary near-tie (retry path)
   int rank_div;        // register-query prefix ranking: first pass over 1/rank_div of the
                        // centroids (a looser bound; 1 after an overflow)
+  bool rank_tight;     // selection with the exact n-th score as its bound (after an overflow)
   bool spec;           // lookahead with speculative issue past the stop line
   int spec_round;      // first round whose update speculates
   int spec_max;        // ranks issued past the stop line, at most
@@ -429,7 +430,8 @@ int rank_queries_in(const sieve_index* ix, const void* queries, int64_t q0, int6
     HIP_TRY(launch_rank_scores(ix->dtype, queries, q0 + a, c, ix->centroids, ix->nlist, ix->d,
                                scores, s));
     HIP_TRY(launch_rank_select(ix->dtype, queries, q0 + a, c, ix->centroids, ix->nlist, ix->d,
-                               scores, nsel, ix->cmax, P + a * ldp, ldp, rc, pl.wide_rank, s));
+                               scores, nsel, ix->cmax, P + a * ldp, ldp, rc, pl.rank_tight, pl.wide_rank,
+                               s));
   }
   return SIEVE_OK;
 }
@@ -776,10 +778,12 @@ int search_impl(sieve_index* ix, const void* queries, int64_t nq, const int64_t*
       sm.hits = ix->rc_host->hits;
     }
     if (sm.rank_error) {
-      // a query's rank candidates overflowed: first with the first pass over
-      // every centroid (the tight bound), then with the wide buffers
-      if (pl.rank_div > 1 && !pl.wide_rank) {
+      // a query's rank candidates overflowed: first with the tight bounds (the
+      // first pass over every centroid, the exact n-th score), then with the
+      // wide buffers
+      if (!pl.rank_tight && !pl.wide_rank) {
         pl.rank_div = 1;
+        pl.rank_tight = true;
         continue;
       }
       if (pl.wide_rank)
@@ -924,6 +928,7 @@ int plan_search(const sieve_index* ix, int64_t nq, int32_t k, float tau, int32_t
   pl->group_q = pl->tile_q;
   pl->min_group = pl->rega ? scan_rega_tile_q(false) : pl->tile_q;
   pl->wide_rank = false;
+  pl->rank_tight = false;
   // the register-query prefix ranking bounds the R-th score from the first
   // half of the centroids (any subset's R-th largest score is a valid lower
   // bound); a query whose candidates then overflow re-ranks with the full pass
@@ -1283,9 +1288,9 @@ SIEVE_API int sieve_rank(const sieve_index* idx, const void* queries, int64_t nq
   RoundCounters* rc = (RoundCounters*)ix->rc.p;
   const int div0 = pl.rank_div;
   for (int attempt = 0; attempt < 3; ++attempt) {
-    // the first pass over a subset, then over every centroid, then wide buffers
-    if (attempt == 1 && div0 <= 1) continue;
+    // loose bounds, tight ones (see search_impl), then wide buffers
     pl.rank_div = attempt == 0 ? div0 : 1;
+    pl.rank_tight = attempt == 1;
     pl.wide_rank = attempt == 2;
     HIP_TRY(launch_zero_bytes(rc, sizeof(RoundCounters), s));
     if ((st = rank_queries(ix, queries, 0, nq, pl.n, pl.n, pl, out_order, s))) return st;
@@ -1359,9 +1364,9 @@ SIEVE_API int sieve_rank_noalloc(const sieve_index* idx, const void* queries, in
   const size_t ws_bytes = kScratchBytes - kHead;
   const int div0 = pl.rank_div;
   for (int attempt = 0; attempt < 3; ++attempt) {
-    // the first pass over a subset, then over every centroid, then wide buffers
-    if (attempt == 1 && div0 <= 1) continue;
+    // loose bounds, tight ones (see search_impl), then wide buffers
     pl.rank_div = attempt == 0 ? div0 : 1;
+    pl.rank_tight = attempt == 1;
     pl.wide_rank = attempt == 2;
     // queries per chunk that fit the workspace
     unsigned long long* cand = nullptr;

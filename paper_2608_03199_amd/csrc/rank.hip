@@ -232,15 +232,21 @@ __global__ __launch_bounds__(NT) void rank_select_kernel(
 // that few keys more than n reach: the candidates are then all scores >= t -
 // 2 delta, a superset of those >= v - 2 delta, and the exact order of the
 // first n is the same.  About 14 steps instead of 32, for this many more
-// candidates to sort at most.
-__device__ __forceinline__ int rank_excess(int n) { return 8 + n / 8; }
+// candidates to sort at most.  The candidate buffers have room for them on
+// top of the near-ties.  Where more near-ties than that lie around t, the
+// caller ranks again with v itself (excess < 0: no early stop, no lane
+// maxima) before it takes the wide buffers (5,000 queries with 560 ties just
+// under t, 3,000 centroids: 269 us; 477 when the wide buffers came next).
+__host__ __device__ inline int rank_excess(int n) { return 8 + n / 8; }
+// More keys than n that may reach the lane maxima's bound.
+constexpr int kLaneExcess = 32;
 
 // One query per block of 256 threads, its screen scores held in registers
 // (KPT per thread, nlist <= 256 * KPT): long prefixes over large centroid
 // sets, where one wave per query would hold too many keys.
 //   1. the n-th largest key is bounded from below bit by bit (each step counts
 //      keys >= the candidate prefix with ballot popcounts per wave and one
-//      LDS exchange between the four waves; see rank_excess);
+//      LDS exchange between the four waves; excess: see rank_excess);
 //   2. candidates (s32 >= v - 2 delta) are compacted with ballots into LDS;
 //   3. they are sorted by counting, near-tie runs are re-scored in fp64
 //      (waves of the block share the members), and the first n are written.
@@ -249,7 +255,7 @@ template <int DT, int KPT>
 __global__ __launch_bounds__(256) void rank_select_reg_kernel(
     const void* __restrict__ queries, int64_t q0, const void* __restrict__ centroids,
     int32_t nlist, int32_t d, const float* __restrict__ scores, int32_t n, int32_t cap,
-    double cmax, int32_t* __restrict__ P, int64_t ldp, RoundCounters* rc) {
+    int32_t excess, double cmax, int32_t* __restrict__ P, int64_t ldp, RoundCounters* rc) {
   extern __shared__ uint8_t smem[];
   unsigned long long* ck = (unsigned long long*)smem;  // [cap]
   unsigned long long* out = ck + cap;                  // [cap]
@@ -297,7 +303,7 @@ __global__ __launch_bounds__(256) void rank_select_reg_kernel(
                       s_cnt[bit & 1][3];
     if (total >= n) {
       prefix = cand;
-      if (total <= n + rank_excess(n)) break;  // uniform over the block
+      if (total <= n + excess) break;  // uniform over the block
     }
   }
   const double lo = (double)key2f(prefix) - gap;
@@ -367,7 +373,7 @@ constexpr int kKeysPerLane = 8;
 //    score) is bounded from below.  Up to kLaneRanks ranks: the n-th largest
 //    of the 64 lane maxima (n lanes hold a key that reaches it; about 1.4 n
 //    keys do), found bit by bit with one ballot a step.  More ranks: bit by
-//    bit over all keys, until few more than n reach the prefix (rank_excess);
+//    bit over all keys, until few more than n reach the prefix (excess);
 // 3. candidates (score >= v - 2 delta) are compacted with ballots;
 // 4. they are sorted exactly by counting; near-tie runs get fp64 scores and
 //    an insertion sort, as in the block kernel.
@@ -377,7 +383,7 @@ template <int DT, int KPL>
 __global__ __launch_bounds__(256) void rank_select_wave_kernel(
     const void* __restrict__ queries, int64_t q0, int32_t nqc, const void* __restrict__ centroids,
     int32_t nlist, int32_t d, const float* __restrict__ scores, int32_t n, int32_t capw,
-    double cmax, int32_t* __restrict__ P, int64_t ldp, RoundCounters* rc) {
+    int32_t excess, double cmax, int32_t* __restrict__ P, int64_t ldp, RoundCounters* rc) {
   extern __shared__ uint8_t smem[];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int64_t ql = (int64_t)blockIdx.x * 4 + wave;
@@ -415,7 +421,7 @@ __global__ __launch_bounds__(256) void rank_select_wave_kernel(
   // it stays in scalar registers (no cross-lane shuffles)
   uint32_t prefix = 0;
   int reach = 0x7fffffff;  // keys that reach the prefix of the lane maxima
-  if (n <= kLaneRanks && nlist >= 64) {
+  if (excess >= 0 && n <= kLaneRanks && nlist >= 64) {
     uint32_t kmax = key[0];
 #pragma unroll
     for (int j = 1; j < KPL; ++j) kmax = max(kmax, key[j]);
@@ -427,7 +433,7 @@ __global__ __launch_bounds__(256) void rank_select_wave_kernel(
 #pragma unroll
     for (int j = 0; j < KPL; ++j) reach += __popcll(__ballot(key[j] >= prefix));
   }
-  if (reach > n + 64) {  // more ranks, or large keys crowded on few lanes
+  if (reach > n + kLaneExcess) {  // more ranks, or large keys crowded on few lanes
     prefix = 0;
     for (int bit = 31; bit >= 0; --bit) {
       const uint32_t cand = prefix | (1u << bit);
@@ -436,7 +442,7 @@ __global__ __launch_bounds__(256) void rank_select_wave_kernel(
       for (int j = 0; j < KPL; ++j) cnt += __popcll(__ballot(key[j] >= cand));
       if (cnt >= n) {
         prefix = cand;
-        if (cnt <= n + rank_excess(n)) break;
+        if (cnt <= n + excess) break;
       }
     }
   }
@@ -477,7 +483,7 @@ size_t rank_select_lds(int32_t nlist, int32_t cap) {
 template <int DT, int KPL>
 hipError_t launch_wave_t(const void* queries, int64_t q0, int32_t nqc, const void* centroids,
                          int32_t nlist, int32_t d, const float* scores, int32_t n, int32_t capw,
-                         double cmax, int32_t* P, int64_t ldp, RoundCounters* rc,
+                         int32_t excess, double cmax, int32_t* P, int64_t ldp, RoundCounters* rc,
                          hipStream_t s) {
   const size_t lds = (size_t)4 * wave_region_bytes(capw);
   static const hipError_t attr =
@@ -487,53 +493,62 @@ hipError_t launch_wave_t(const void* queries, int64_t q0, int32_t nqc, const voi
   if (lds > 150 * 1024) return hipErrorInvalidValue;
   hipLaunchKernelGGL((rank_select_wave_kernel<DT, KPL>), dim3((unsigned)((nqc + 3) / 4)),
                      dim3(256), lds, s, queries, q0, nqc, centroids, nlist, d, scores, n, capw,
-                     cmax, P, ldp, rc);
+                     excess, cmax, P, ldp, rc);
   return hipGetLastError();
 }
 
 template <int DT>
 hipError_t launch_wave(const void* queries, int64_t q0, int32_t nqc, const void* centroids,
                        int32_t nlist, int32_t d, const float* scores, int32_t n, int32_t capw,
-                       double cmax, int32_t* P, int64_t ldp, RoundCounters* rc,
+                       int32_t excess, double cmax, int32_t* P, int64_t ldp, RoundCounters* rc,
                        hipStream_t s) {
   if (nlist <= 256)
-    return launch_wave_t<DT, 4>(queries, q0, nqc, centroids, nlist, d, scores, n, capw, cmax,
-                                  P, ldp, rc, s);
+    return launch_wave_t<DT, 4>(queries, q0, nqc, centroids, nlist, d, scores, n, capw, excess,
+                                  cmax, P, ldp, rc, s);
   if (nlist <= 512)
-    return launch_wave_t<DT, 8>(queries, q0, nqc, centroids, nlist, d, scores, n, capw, cmax,
-                                  P, ldp, rc, s);
+    return launch_wave_t<DT, 8>(queries, q0, nqc, centroids, nlist, d, scores, n, capw, excess,
+                                  cmax, P, ldp, rc, s);
   if (nlist <= 1024)
-    return launch_wave_t<DT, 16>(queries, q0, nqc, centroids, nlist, d, scores, n, capw, cmax,
-                                  P, ldp, rc, s);
-  return launch_wave_t<DT, 64>(queries, q0, nqc, centroids, nlist, d, scores, n, capw, cmax,
-                                 P, ldp, rc, s);
+    return launch_wave_t<DT, 16>(queries, q0, nqc, centroids, nlist, d, scores, n, capw, excess,
+                                  cmax, P, ldp, rc, s);
+  return launch_wave_t<DT, 64>(queries, q0, nqc, centroids, nlist, d, scores, n, capw, excess,
+                                 cmax, P, ldp, rc, s);
 }
 
 hipError_t launch_rank_select(int dtype, const void* queries, int64_t q0, int32_t nqc,
                               const void* centroids, int32_t nlist, int32_t d, const float* scores,
                               int32_t n, double cmax, int32_t* P, int64_t ldp, RoundCounters* rc,
-                              bool wide, hipStream_t s) {
+                              bool tight, bool wide, hipStream_t s) {
   if (nqc <= 0) return hipSuccess;
+  const int32_t excess = tight ? -1 : rank_excess(n);
   // one wave per query while the boundary buffer stays small
   const int elem = dtype == SIEVE_F32 ? 4 : 2;
-  int capw = n + 128 < nlist ? n + 128 : nlist;
+  static_assert(kLaneExcess >= 8 + kLaneRanks / 8, "room for either bound's excess");
+  // (room for the excess as far as it does not move n to another kernel)
+  constexpr int kWaveCap = 64 * kKeysPerLane;
+  const int more = n <= kLaneRanks ? kLaneExcess : rank_excess(n);
+  const int capw = std::min(n + 128 <= kWaveCap ? std::min(n + 128 + more, kWaveCap) : n + 128,
+                            nlist);
   if (!wide && nlist <= 1024 && capw <= 64 * kKeysPerLane &&
       4 * wave_region_bytes(capw) <= 96 * 1024) {
     return dtype == SIEVE_F32
                ? launch_wave<SIEVE_F32>(queries, q0, nqc, centroids, nlist, d, scores, n, capw,
-                                        cmax, P, ldp, rc, s)
+                                        excess, cmax, P, ldp, rc, s)
                : launch_wave<SIEVE_F16>(queries, q0, nqc, centroids, nlist, d, scores, n, capw,
-                                        cmax, P, ldp, rc, s);
+                                        excess, cmax, P, ldp, rc, s);
   }
   // register-resident block kernel: large centroid sets, narrow buffer
   if (!wide && nlist > 1024 && nlist <= 256 * 64) {
-    const int32_t capr = n + 512 < nlist ? n + 512 : nlist;
+    constexpr int kRegCap = 64 * 1024 / 25;
+    const int32_t capr =
+        std::min(n + 512 <= kRegCap ? std::min(n + 512 + rank_excess(n), kRegCap) : n + 512,
+                 nlist);
     const size_t ldsr = (size_t)capr * 25;
     if (ldsr <= 64 * 1024) {
       const int kpt = nlist <= 256 * 16 ? 16 : (nlist <= 256 * 32 ? 32 : 64);
 #define SIEVE_REG(DT, K)                                                                       \
   hipLaunchKernelGGL((rank_select_reg_kernel<DT, K>), dim3(nqc), dim3(256), ldsr, s, queries, q0, \
-                     centroids, nlist, d, scores, n, capr, cmax, P, ldp, rc)
+                     centroids, nlist, d, scores, n, capr, excess, cmax, P, ldp, rc)
       if (dtype == SIEVE_F32) {
         if (kpt == 16) SIEVE_REG(SIEVE_F32, 16);
         else if (kpt == 32) SIEVE_REG(SIEVE_F32, 32);

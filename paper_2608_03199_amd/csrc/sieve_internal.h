@@ -305,7 +305,7 @@ hipError_t launch_rank_prefix(int dtype, const void* queries, int64_t q0, int32_
 hipError_t launch_rank_select(int dtype, const void* queries, int64_t q0, int32_t nqc,
                               const void* centroids, int32_t nlist, int32_t d, const float* scores,
                               int32_t n, double cmax, int32_t* P, int64_t ldp, RoundCounters* rc,
-                              bool wide, hipStream_t s);
+                              bool tight, bool wide, hipStream_t s);
 
 hipError_t launch_emit_initial(const int32_t* P, int32_t n, int64_t nqc, int32_t q0, int32_t s0,
                                int32_t mode, Item* items, int64_t item_cap, int32_t* cnt,
