@@ -334,6 +334,10 @@ bool arena_on(const sieve_index* ix) {
 }
 int spill_grid(const sieve_index* ix) { return ((2 * ix->cus + 7) / 8) * 8; }
 
+// Tiles past the bound of a search's widest round, for small rounds that split
+// their lists (screen_rows_per_tile).
+constexpr int64_t kTileSlack = 4096;
+
 int grow_workspace(sieve_index* ix, const SearchPlan& pl) {
   const int64_t nq = pl.nq;
   const int n = pl.n;
@@ -348,7 +352,7 @@ int grow_workspace(sieve_index* ix, const SearchPlan& pl) {
   const int64_t max_ch = (ix->max_list + chunk - 1) / chunk;
   const int64_t tile_cap = pl.item_cap / std::min(pl.group_q, pl.min_group) *
                                (max_ch > 0 ? max_ch : 1) +
-                           ix->nlist + ix->n / chunk + 16;
+                           ix->nlist + ix->n / chunk + kTileSlack;
   if (tile_cap > INT32_MAX) return fail(SIEVE_EUNSUPPORTED, "tile count bound overflows int32");
   if ((st = ensure(ix, ix->tiles, (size_t)tile_cap * sizeof(Tile)))) return st;
   const size_t nl = (size_t)ix->nlist;
@@ -497,10 +501,16 @@ int run_round(sieve_index* ix, const ScanArgs& sa, int n_items, int64_t q0, cons
   const bool dense = (int64_t)n_items >= (int64_t)pl.dense_q * ix->nlist;
   int chunk = dense ? pl.row_chunk_dense : pl.row_chunk;
   int group = pl.group_q, tile_q = pl.tile_q, grid = pl.scan_grid;
+  const int64_t tile_cap = (int64_t)(ix->tiles.bytes / sizeof(Tile));
   if (pl.screen) {
-    chunk = dense ? pl.s_chunk_dense : pl.s_chunk;
     group = tile_q = screen_tile_q(ix->d, dense);
     grid = ((ix->cus * screen_grid_per_cu(ix->d, dense) + 7) / 8) * 8;
+    // a tile per work-group; where the queries are staged in LDS, one for every
+    // other (128 lists of 781 rows, 768 dimensions, 128 queries each: 43 us in
+    // 128 tiles, 51 in 256)
+    chunk = screen_rows_per_tile(dense ? pl.s_chunk_dense : pl.s_chunk,
+                                 ix->d <= 128 ? grid : grid / 2, n_items, group, ix->nlist, ix->n,
+                                 ix->max_list, tile_cap);
   } else if (pl.rega) {
     // dense rounds: 128-query tiles of whole lists, one work-group per CU;
     // sparse rounds: 64-query tiles of 512 rows, two per CU
@@ -512,7 +522,6 @@ int run_round(sieve_index* ix, const ScanArgs& sa, int n_items, int64_t q0, cons
   }
   const int e0 = *at >= 0 ? *at : mark(ix, timed, s);
   // few lists: the offsets launch also writes the tiles
-  const int64_t tile_cap = (int64_t)(ix->tiles.bytes / sizeof(Tile));
   const bool fuse = ix->nlist <= kFuseTilesMaxLists;
   HIP_TRY(launch_sched_offsets((int32_t*)ix->cnt.p, ix->offsets, ix->nlist, chunk, group,
                                (int32_t*)ix->item_off.p, (int32_t*)ix->cursor.p,
