@@ -57,10 +57,48 @@ struct Buf {
   size_t bytes = 0;
 };
 
+int index_device(const sieve_index* ix);
+
+// The indexes that hold an 8-bit copy of their rows (the screened scan reads
+// it; searches return the same without it).  An allocation of the library that
+// does not fit takes copies back, the own index's first, so that whatever fits
+// without the copies fits with them.
+struct Copies {
+  std::mutex mu;
+  std::vector<sieve_index*> held;
+};
+Copies& copies() {
+  static Copies* c = new Copies;  // never destroyed: handles may outlive it
+  return *c;
+}
+// Free one copy: own's, else one on the device that no search is reading;
+// false where there is none.  only_look: free nothing.
+bool give_copy_back(sieve_index* own, int device, bool only_look = false);
+
+// hipMalloc, taking copies back while it fails.  SIEVE_COPY_ALLOC_CAP (bytes)
+// refuses larger allocations as long as there is a copy to take (tests).
+hipError_t dev_alloc(void** p, size_t bytes, sieve_index* own, int device) {
+  const char* knob = getenv("SIEVE_COPY_ALLOC_CAP");
+  const bool refuse = knob && bytes > strtoull(knob, nullptr, 10);
+  for (;;) {
+    const hipError_t e =
+        refuse && give_copy_back(own, device, true) ? hipErrorOutOfMemory : hipMalloc(p, bytes);
+    if (e == hipSuccess) return e;
+    *p = nullptr;
+    (void)hipGetLastError();
+    if (!give_copy_back(own, device)) return e;
+  }
+}
+template <typename T>
+hipError_t dev_alloc(T** p, size_t bytes, sieve_index* own, int device) {
+  return dev_alloc((void**)p, bytes, own, device);
+}
+
 // SIEVE_ALLOC_CAP (bytes) refuses any single workspace buffer above it with
 // SIEVE_ENOMEM before hipMalloc is called (tests of the out-of-memory path;
-// the buffer already held stays valid).
-int ensure(Buf& b, size_t bytes) {
+// the buffer already held stays valid).  own: null, or an index whose 8-bit
+// copy goes where the buffer does not fit (then other indexes' copies).
+int ensure(Buf& b, size_t bytes, sieve_index* own = nullptr) {
   if (bytes == 0) bytes = 16;
   if (b.bytes >= bytes) return SIEVE_OK;
   if (const char* cap = getenv("SIEVE_ALLOC_CAP")) {
@@ -72,7 +110,7 @@ int ensure(Buf& b, size_t bytes) {
   if (b.p) (void)hipFree(b.p);
   b.p = nullptr;
   b.bytes = 0;
-  hipError_t e = hipMalloc(&b.p, bytes);
+  hipError_t e = own ? dev_alloc(&b.p, bytes, own, index_device(own)) : hipMalloc(&b.p, bytes);
   if (e != hipSuccess) {
     b.p = nullptr;
     (void)hipGetLastError();
@@ -104,6 +142,8 @@ struct sieve_index {
   // scan), or null
   void* v8 = nullptr;
   ScreenParam* lpar = nullptr;
+  int copy_in_use = 0;     // searches that may be reading them (under copies().mu)
+  bool copy_built = false; // it was there when the index was loaded
   // for the estimate of the pairs that pass the screen: its usual slack (twice
   // the lists' mean err times their mean norm) and the scores of sampled row
   // pairs of one list, ascending
@@ -144,19 +184,47 @@ struct sieve_index {
 
 namespace {
 
-// The same for a workspace buffer of an index.  Where device memory runs out
-// the index gives its 8-bit copy back and goes on with exact scans: a search
-// needs no more memory than without the copy.  (hipFree waits for the device.)
-int ensure(sieve_index* ix, Buf& b, size_t bytes) {
-  int st = ensure(b, bytes);
-  if (st != SIEVE_ENOMEM || !ix->v8 || getenv("SIEVE_ALLOC_CAP")) return st;
-  for (void* p : {ix->v8, (void*)ix->lpar, ix->q8.p, ix->qpar.p})
+int index_device(const sieve_index* ix) { return ix->device; }
+
+bool give_copy_back(sieve_index* own, int device, bool only_look) {
+  Copies& c = copies();
+  std::lock_guard<std::mutex> g(c.mu);
+  sieve_index* from = nullptr;
+  for (sieve_index* ix : c.held)
+    if (ix == own || (!from && ix->device == device && ix->copy_in_use == 0)) {
+      from = ix;
+      if (ix == own) break;
+    }
+  if (!from || only_look) return from != nullptr;
+  // (hipFree waits for the device)
+  for (void* p : {from->v8, (void*)from->lpar, from->q8.p, from->qpar.p})
     if (p) (void)hipFree(p);
-  ix->v8 = nullptr;
-  ix->lpar = nullptr;
-  ix->q8 = ix->qpar = Buf{};
-  return ensure(b, bytes);
+  from->v8 = nullptr;
+  from->lpar = nullptr;
+  from->q8 = from->qpar = Buf{};
+  c.held.erase(std::find(c.held.begin(), c.held.end(), from));
+  return true;
 }
+
+// A workspace buffer of an index; where memory runs out the index gives its
+// 8-bit copy back and goes on with exact scans: a search needs no more memory
+// than without the copy.
+int ensure(sieve_index* ix, Buf& b, size_t bytes) { return ensure(b, bytes, ix); }
+
+// While a search runs, only its own allocations take its index's copy.
+struct CopyInUse {
+  sieve_index* ix;
+  explicit CopyInUse(sieve_index* i) : ix(i) {
+    std::lock_guard<std::mutex> g(copies().mu);
+    ++ix->copy_in_use;
+  }
+  ~CopyInUse() {
+    std::lock_guard<std::mutex> g(copies().mu);
+    --ix->copy_in_use;
+  }
+  CopyInUse(const CopyInUse&) = delete;
+  CopyInUse& operator=(const CopyInUse&) = delete;
+};
 
 int elem_bytes(int dtype) { return dtype == SIEVE_F32 ? 4 : 2; }
 
@@ -338,7 +406,7 @@ int spill_grid(const sieve_index* ix) { return ((2 * ix->cus + 7) / 8) * 8; }
 // their lists (screen_rows_per_tile).
 constexpr int64_t kTileSlack = 4096;
 
-int grow_workspace(sieve_index* ix, const SearchPlan& pl) {
+int grow_buffers(sieve_index* ix, const SearchPlan& pl) {
   const int64_t nq = pl.nq;
   const int n = pl.n;
   const int64_t rank_rows = pl.mode == 2 ? pl.fix_chunk : nq;
@@ -350,9 +418,10 @@ int grow_workspace(sieve_index* ix, const SearchPlan& pl) {
   // tiles: sum_p ceil(c_p / tq) * ceil(len_p / rc) <= items * max_chunks / tq + lists + rows / rc
   const int chunk = pl.screen ? std::min(pl.row_chunk, pl.s_chunk) : pl.row_chunk;
   const int64_t max_ch = (ix->max_list + chunk - 1) / chunk;
-  const int64_t tile_cap = pl.item_cap / std::min(pl.group_q, pl.min_group) *
-                               (max_ch > 0 ? max_ch : 1) +
-                           ix->nlist + ix->n / chunk + kTileSlack;
+  const int group = std::min(pl.group_q, pl.screen ? std::min(pl.min_group, screen_tile_q(ix->d, false))
+                                                   : pl.min_group);
+  const int64_t tile_cap = pl.item_cap / group * (max_ch > 0 ? max_ch : 1) + ix->nlist +
+                           ix->n / chunk + (pl.screen ? kTileSlack : 16);
   if (tile_cap > INT32_MAX) return fail(SIEVE_EUNSUPPORTED, "tile count bound overflows int32");
   if ((st = ensure(ix, ix->tiles, (size_t)tile_cap * sizeof(Tile)))) return st;
   const size_t nl = (size_t)ix->nlist;
@@ -367,9 +436,6 @@ int grow_workspace(sieve_index* ix, const SearchPlan& pl) {
       (st = ensure(ix, ix->hoff, (size_t)nq * 8)) || (st = ensure(ix, ix->hcur, (size_t)nq * 8)))
     return st;
   if (pl.spec && (st = ensure(ix, ix->spec_bits, (size_t)nq * pl.hit_words * 4))) return st;
-  if (pl.screen && ((st = ensure(ix, ix->q8, (size_t)nq * screen_chunks(ix->d) * 64)) ||
-                    (st = ensure(ix, ix->qpar, (size_t)nq * sizeof(ScreenParam)))))
-    return st;
   if ((st = ensure(ix, ix->rlog, (size_t)kMaxLogRounds * sizeof(RoundSnap)))) return st;
   // The pool holds at most k entries per (query, tile); most searches need far
   // fewer, so it starts small and grows (the search is then re-run) only when
@@ -398,6 +464,31 @@ int grow_workspace(sieve_index* ix, const SearchPlan& pl) {
     HIP_TRY(hipHostGetDevicePointer((void**)&ix->rs_dev, ix->rs_host, 0));
   }
   return SIEVE_OK;
+}
+
+// The workspace of a search.  The screen takes what is left: where its own
+// buffers do not fit, or the copy went to make room, the search is exact and
+// its buffers have the exact search's sizes.
+int grow_workspace(sieve_index* ix, SearchPlan& pl) {
+  if (!ix->v8) pl.screen = false;
+  int st = grow_buffers(ix, pl);
+  if (!pl.screen) return st;
+  if (st == SIEVE_OK && ix->v8) {
+    if (ensure(ix->q8, (size_t)pl.nq * screen_chunks(ix->d) * 64) == SIEVE_OK &&
+        ensure(ix->qpar, (size_t)pl.nq * sizeof(ScreenParam)) == SIEVE_OK)
+      return SIEVE_OK;
+    for (Buf* b : {&ix->q8, &ix->qpar}) {
+      if (b->p) (void)hipFree(b->p);
+      *b = Buf{};
+    }
+  }
+  pl.screen = false;
+  if (st != SIEVE_OK && st != SIEVE_ENOMEM && st != SIEVE_EUNSUPPORTED) return st;
+  g_err.clear();
+  if (st == SIEVE_OK) return st;
+  if (ix->tiles.p) (void)hipFree(ix->tiles.p);
+  ix->tiles = Buf{};
+  return grow_buffers(ix, pl);
 }
 
 // Centroid order of queries [q0, q0 + cnt) into P (row-major [cnt][n]).
@@ -545,6 +636,7 @@ int run_round(sieve_index* ix, const ScanArgs& sa, int n_items, int64_t q0, cons
     sc.v8 = ix->v8;
     sc.q8 = ix->q8.p;
     sc.dtype = ix->dtype;
+    sc.thr_unit = thr_unit(ix->d);
     // the spill buffer's share of each work-group (an even entry count)
     while (sc.spill_cap > 0 &&
            (size_t)grid * arena_block_entries(sc.spill_cap) * sizeof(TileSpill) > ix->spill.bytes)
@@ -628,6 +720,7 @@ int search_impl(sieve_index* ix, const void* queries, int64_t nq, const int64_t*
     return fail(SIEVE_EINVAL, "current device %d differs from the index's device %d", dev,
                 ix->device);
   const bool timed = stats != nullptr;
+  const CopyInUse in_use(ix);
   if ((st = grow_workspace(ix, pl))) return st;
 
   RoundCounters* rc = (RoundCounters*)ix->rc.p;
@@ -964,7 +1057,7 @@ int plan_search(const sieve_index* ix, int64_t nq, int32_t k, float tau, int32_t
   // against the same limit as it runs.  SIEVE_SCREEN = 0 turns them off, 2
   // forces them in every round where the copy exists (tests).
   const int scr = env_count("SIEVE_SCREEN", 1);
-  pl->screen = ix->v8 && scr != 0 && arena_on(ix);
+  pl->screen = ix->copy_built && scr != 0 && arena_on(ix);
   pl->screen_forced = scr == 2;
   if (pl->screen && !pl->screen_forced) {
     const auto& v = ix->scr_scores;
@@ -983,7 +1076,6 @@ int plan_search(const sieve_index* ix, int64_t nq, int32_t k, float tau, int32_t
     };
     pl->s_chunk = rows("SIEVE_SCREEN_CHUNK", reg ? 2048 : 1024);
     pl->s_chunk_dense = std::max(pl->s_chunk, rows("SIEVE_SCREEN_CHUNK_DENSE", reg ? whole : 4096));
-    if (pl->screen) pl->min_group = std::min(pl->min_group, screen_tile_q(ix->d, false));
   }
   // Speculative issue needs the rank packed beside the query in pool entries
   // (queries < 2^kRankShift) and a stop rule that can stop early (W < n).
@@ -1126,13 +1218,14 @@ SIEVE_API int sieve_load_index(const void* vectors, int32_t dtype, int64_t n, in
   for (int l = 0; l < nlist; ++l) hfoff[l + 1] = hfoff[l] + (off[l + 1] - off[l] + 15) / 16 * 16;
   const size_t vfbytes = vector_frag_bytes(dtype, d, hfoff[nlist]);
   hipError_t err;
-  if ((err = hipMalloc(&ix->vectors, vbytes ? vbytes : 16)) != hipSuccess ||
-      (err = hipMalloc((void**)&ix->offsets, sizeof(int64_t) * (nlist + 1))) != hipSuccess ||
-      (err = hipMalloc((void**)&ix->ids, n > 0 ? sizeof(int64_t) * n : 16)) != hipSuccess ||
-      (err = hipMalloc(&ix->centroids, cbytes)) != hipSuccess ||
-      (fbytes && (err = hipMalloc(&ix->cfrag, fbytes)) != hipSuccess) ||
-      (vfbytes && (err = hipMalloc(&ix->vfrag, vfbytes)) != hipSuccess) ||
-      (err = hipMalloc((void**)&ix->foff, sizeof(int64_t) * (nlist + 1))) != hipSuccess) {
+  auto alloc = [&](auto** p, size_t bytes) {
+    return (err = dev_alloc(p, bytes, ix, dev)) == hipSuccess;
+  };
+  if (!alloc(&ix->vectors, vbytes ? vbytes : 16) ||
+      !alloc(&ix->offsets, sizeof(int64_t) * (nlist + 1)) ||
+      !alloc(&ix->ids, n > 0 ? sizeof(int64_t) * n : 16) || !alloc(&ix->centroids, cbytes) ||
+      (fbytes && !alloc(&ix->cfrag, fbytes)) || (vfbytes && !alloc(&ix->vfrag, vfbytes)) ||
+      !alloc(&ix->foff, sizeof(int64_t) * (nlist + 1))) {
     (void)hipGetLastError();
     return bail(fail(SIEVE_ENOMEM, "index allocation failed: %s", hipGetErrorString(err)));
   }
@@ -1145,22 +1238,26 @@ SIEVE_API int sieve_load_index(const void* vectors, int32_t dtype, int64_t n, in
                             hipMemcpyHostToDevice, s)) != hipSuccess)
     return bail(fail(SIEVE_EDEVICE, "index copy failed: %s", hipGetErrorString(err)));
   // The 8-bit copy of the screened scan is taken where it fits well (at most a
-  // third of what is free now); without it every scan is exact.
+  // third of what is free now); without it every scan is exact.  SIEVE_SCREEN =
+  // 0 at load declines it.
   std::vector<ScreenParam> hl;
   std::vector<float> hs;
-  if (screen_chunks(d) > 0 && n > 0) {
+  if (screen_chunks(d) > 0 && n > 0 && env_count("SIEVE_SCREEN", 1) != 0) {
     const size_t sbytes = screen_rows_bytes(d, hfoff[nlist]);
     size_t mfree = 0, mtotal = 0;
     if (hipMemGetInfo(&mfree, &mtotal) == hipSuccess && sbytes <= mfree / 3 &&
         hipMalloc((void**)&ix->lpar, sizeof(ScreenParam) * nlist) == hipSuccess &&
-        ensure(ix, ix->scores, (size_t)kScreenSample * 256 * sizeof(float)) == SIEVE_OK &&
+        ensure(ix->scores, (size_t)kScreenSample * 256 * sizeof(float)) == SIEVE_OK &&
         hipMalloc(&ix->v8, sbytes) == hipSuccess) {
       hl.resize(nlist);
       hs.resize((size_t)kScreenSample * 256);
     } else {
       (void)hipGetLastError();
-      if (ix->v8) (void)hipFree(ix->v8);
+      g_err.clear();
+      for (void* p : {ix->v8, (void*)ix->lpar})
+        if (p) (void)hipFree(p);
       ix->v8 = nullptr;
+      ix->lpar = nullptr;
     }
   }
   if ((err = launch_index_rows(dtype, d, ix->vectors, ix->offsets, ix->foff, nlist, hfoff[nlist],
@@ -1204,12 +1301,22 @@ SIEVE_API int sieve_load_index(const void* vectors, int32_t dtype, int64_t n, in
     }
   }
   if (!isfinite(ix->cmax)) return bail(fail(SIEVE_EINVAL, "centroids contain inf or NaN"));
+  if (ix->v8) {
+    ix->copy_built = true;
+    std::lock_guard<std::mutex> g(copies().mu);
+    copies().held.push_back(ix);
+  }
   *out = ix;
   return SIEVE_OK;
 }
 
 SIEVE_API void sieve_free_index(sieve_index* ix) {
   if (!ix) return;
+  {
+    std::lock_guard<std::mutex> g(copies().mu);
+    auto& h = copies().held;
+    h.erase(std::remove(h.begin(), h.end(), ix), h.end());
+  }
 #define SIEVE_FREE_BUF(name) \
   if (ix->name.p) (void)hipFree(ix->name.p);
   SIEVE_WORKSPACE(SIEVE_FREE_BUF)

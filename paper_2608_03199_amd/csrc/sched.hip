@@ -236,21 +236,37 @@ __global__ __launch_bounds__(kOffThreads) void sched_offsets_kernel(
 
 // The smallest 8-bit product of a (query, list) pair whose score may reach
 // tau (the bound is derived in screen_tile.h): floor((tau - slack) / (s_q s_l)),
-// held inside +-2^28, which no product of at most 1,024 dimensions leaves.  A
-// bound that is not a number, or norms whose product could overflow fp32 on
-// the way to a score, give -2^28 (every pair is scored).
-constexpr double kThrLim = 268435456.0;
+// in the packed items' units and held inside their range, whose smallest value
+// no product falls below (see BItem).  A bound that is not a number, or norms
+// whose product could overflow fp32 on the way to a score, give that value
+// (every pair is scored).
 constexpr double kScoreUnderflow = 1.1754943508222875e-38;  // 2^-126
 __device__ __forceinline__ int32_t screen_threshold(const ScreenParam& q, const ScreenParam& l,
-                                                    float tau, int32_t d) {
+                                                    float tau, int32_t d, int32_t unit) {
   const double nq = (double)q.norm + (double)q.err;  // >= |q|
   const double slack = (double)q.norm * l.err + (double)q.err * l.norm +
                        2.0 * (double)(d + 2) * 5.9604644775390625e-08 * nq * l.norm +
                        kScoreUnderflow * (double)d * (2.0 + nq + l.norm);
-  const double t = ((double)tau - slack) / ((double)q.s * (double)l.s);
-  if (!(nq * l.norm < 1e37)) return -(int32_t)kThrLim;
-  if (!(t > -kThrLim)) return -(int32_t)kThrLim;
-  return t < kThrLim ? (int32_t)floor(t) : (int32_t)kThrLim;
+  const double t = ((double)tau - slack) / ((double)q.s * (double)l.s * (double)(1 << unit));
+  if (!(nq * l.norm < 1e37)) return -kThrMax - 1;
+  if (!(t > (double)-kThrMax)) return -kThrMax - 1;
+  return t < (double)kThrMax ? (int32_t)floor(t) : kThrMax;
+}
+
+// The bucketed item of (query, rank) in list p.
+__device__ __forceinline__ BItem make_bitem(const Item& it, int p,
+                                            const int64_t* __restrict__ exclude,
+                                            const ScreenParam* __restrict__ qpar,
+                                            const ScreenParam* __restrict__ lpar, float tau,
+                                            int32_t d, int32_t unit) {
+  BItem b;
+  b.q = it.q;
+  b.rank = it.rank;
+  if (qpar)
+    b.rank |= (int32_t)((uint32_t)screen_threshold(qpar[it.q], lpar[p], tau, d, unit)
+                        << kThrShift);
+  b.ex = exclude ? exclude[it.q] : INT64_MIN;
+  return b;
 }
 
 __global__ void sched_scatter_kernel(const Item* __restrict__ items, int32_t n_items,
@@ -258,19 +274,14 @@ __global__ void sched_scatter_kernel(const Item* __restrict__ items, int32_t n_i
                                      const int64_t* __restrict__ exclude,
                                      int32_t* __restrict__ cursor, BItem* __restrict__ bucket,
                                      const ScreenParam* __restrict__ qpar,
-                                     const ScreenParam* __restrict__ lpar, float tau, int32_t d) {
+                                     const ScreenParam* __restrict__ lpar, float tau, int32_t d,
+                                     int32_t unit) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= n_items) return;
   const Item it = items[i];
   const int p = P[(int64_t)(it.q - q0) * n + it.rank];
   const int pos = atomicAdd(&cursor[p], 1);
-  BItem b;
-  b.q = it.q;
-  b.rank = it.rank;
-  b.ex = exclude ? exclude[it.q] : INT64_MIN;
-  b.thr = qpar ? screen_threshold(qpar[it.q], lpar[p], tau, d) : 0;
-  b.pad = 0;
-  bucket[pos] = b;
+  bucket[pos] = make_bitem(it, p, exclude, qpar, lpar, tau, d, unit);
 }
 
 // Many items per list: a work-group takes kGroupItems consecutive items,
@@ -285,7 +296,7 @@ __global__ __launch_bounds__(kGroupThreads) void sched_scatter_grouped_kernel(
     const Item* __restrict__ items, int32_t n_items, const int32_t* __restrict__ P, int32_t n,
     int32_t q0, const int64_t* __restrict__ exclude, int32_t* __restrict__ cursor,
     BItem* __restrict__ bucket, const ScreenParam* __restrict__ qpar,
-    const ScreenParam* __restrict__ lpar, float tau, int32_t d, int32_t nlist) {
+    const ScreenParam* __restrict__ lpar, float tau, int32_t d, int32_t unit, int32_t nlist) {
   extern __shared__ int32_t s_cnt[];  // [nlist]: the group's items, then its first slot
   for (int i = threadIdx.x; i < nlist; i += kGroupThreads) s_cnt[i] = 0;
   __syncthreads();
@@ -309,13 +320,7 @@ __global__ __launch_bounds__(kGroupThreads) void sched_scatter_grouped_kernel(
 #pragma unroll
   for (int u = 0; u < kGroupPer; ++u) {
     if (at[u] < 0) continue;
-    BItem b;
-    b.q = it[u].q;
-    b.rank = it[u].rank;
-    b.ex = exclude ? exclude[it[u].q] : INT64_MIN;
-    b.thr = qpar ? screen_threshold(qpar[it[u].q], lpar[p[u]], tau, d) : 0;
-    b.pad = 0;
-    bucket[s_cnt[p[u]] + at[u]] = b;
+    bucket[s_cnt[p[u]] + at[u]] = make_bitem(it[u], p[u], exclude, qpar, lpar, tau, d, unit);
   }
 }
 
@@ -717,17 +722,17 @@ hipError_t launch_sched_scatter(const Item* items, int32_t n_items, const int32_
                                 BItem* bucket, const ScreenParam* qpar, const ScreenParam* lpar,
                                 float tau, int32_t d, int32_t nlist, hipStream_t s) {
   if (n_items <= 0) return hipSuccess;
-  // worth it where a group holds several items of a list; the LDS histogram
-  // (64 KB at most) needs no opt-in
+  const int32_t unit = qpar ? thr_unit(d) : 0;
+  // worth it where a group holds several items of a list
   if (n_items >= 8 * kGroupItems && nlist <= kGroupItems / 2) {
     hipLaunchKernelGGL(sched_scatter_grouped_kernel,
                        dim3((n_items + kGroupItems - 1) / kGroupItems), dim3(kGroupThreads),
                        (size_t)nlist * 4, s, items, n_items, P, n, q0, exclude, cursor, bucket,
-                       qpar, lpar, tau, d, nlist);
+                       qpar, lpar, tau, d, unit, nlist);
     return hipGetLastError();
   }
   hipLaunchKernelGGL(sched_scatter_kernel, dim3(blocks_for(n_items)), dim3(kThreads), 0, s, items,
-                     n_items, P, n, q0, exclude, cursor, bucket, qpar, lpar, tau, d);
+                     n_items, P, n, q0, exclude, cursor, bucket, qpar, lpar, tau, d, unit);
   return hipGetLastError();
 }
 

@@ -18,7 +18,7 @@
 // pair whose score reaches tau has
 //   qi.xi >= T(q, l) = floor((tau - slack) / (s_q s_l)),
 // slack = |q^| e_l + |q - q^| n_l + 2 (d + 2) 2^-24 |q| n_l + u: no such pair
-// is screened out.  Pairs that pass are scored with the exact scan's MFMA
+// is screened out (T is kept in a few bits, rounded down; see BItem).  Pairs that pass are scored with the exact scan's MFMA
 // sequence on the stored values (the same bits) and compared with tau.  Where
 // the bound is not finite (a list or a query with inf or NaN, an overflowing
 // norm) T is below every product: all its pairs are scored.
@@ -390,10 +390,11 @@ __global__ __launch_bounds__(kNT, kOcc) void screen_scan_kernel(ScreenArgs a) {
   auto put_items = [&](int set, const Tile& r, const BItem& it) {
     if ((int)threadIdx.x < kTQ) {
       const bool real = (int)threadIdx.x < r.nq;
-      s_init[set][threadIdx.x] = real ? -it.thr : kInitNever;
+      s_init[set][threadIdx.x] =
+          real ? -((it.rank >> kThrShift) * (1 << a.thr_unit)) : kInitNever;
       if (real) {
         s_q[set][threadIdx.x] = it.q;
-        s_rank[set][threadIdx.x] = it.rank;
+        s_rank[set][threadIdx.x] = it.rank & (kMaxRanks - 1);
         s_ex[set][threadIdx.x] = it.ex;
       }
     }

@@ -29,11 +29,22 @@ struct Tile {
 // everything about its next tile's items with one load per item.
 struct BItem {
   int32_t q;
-  int32_t rank;
-  int64_t ex;   // exclude_ids[q], or INT64_MIN
-  int32_t thr;  // screened scans: smallest 8-bit product that may reach tau
-  int32_t pad;
+  int32_t rank;  // screened scans: rank | threshold << kThrShift
+  int64_t ex;    // exclude_ids[q], or INT64_MIN
 };
+
+// A screened item's threshold, the smallest 8-bit product that may reach tau,
+// is kept beside the rank (< kMaxRanks = 2^kThrShift) as a signed number of 21
+// bits in units of 2^thr_unit(d), rounded down: 127^2 d <= 2^(20 + unit), so
+// the smallest value admits every product, and the rounding is at most 16 of
+// 16.5 million (d = 1,024).  The items take 16 bytes in every kind of round.
+constexpr int kThrShift = 11;
+constexpr int32_t kThrMax = (1 << 20) - 1;  // and -kThrMax - 1 at least
+__host__ __device__ inline int thr_unit(int d) {
+  int u = 0;
+  while ((int64_t)127 * 127 * d > ((int64_t)1 << (20 + u))) ++u;
+  return u;
+}
 
 // Screened scans (screen_tile.h): a list's 8-bit rows are x^ = s xi with
 // |x - x^| <= err and |x| <= norm for every row; a query's 8-bit row is
@@ -61,6 +72,7 @@ constexpr int kRegAQB = 8;
 constexpr int kTileQ = 16 * (kQB > kRegAQB ? kQB : kRegAQB);
 constexpr int kScanThreads = 256;  // 4 wave64
 constexpr int kMaxRanks = 2048;    // largest n = min(nprobe_max, nlist)
+static_assert(kMaxRanks == 1 << kThrShift, "a rank and a threshold share a word");
 constexpr int kMaxNlist = 16384;   // centroid scores of one query fit in LDS
 constexpr int kMaxCand = 4096;     // rank-boundary candidates kept for the exact sort
 constexpr int kMaxD = 4096;
@@ -211,6 +223,7 @@ struct ScreenArgs : ScanArgs {
   const void* v8 = nullptr;
   const void* q8 = nullptr;
   int32_t dtype = 0;
+  int32_t thr_unit = 0;  // of the items' thresholds
 };
 
 // Query rows per tile for a dtype and dimension: as many 16-row blocks (<= 8)
