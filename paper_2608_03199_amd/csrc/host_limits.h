@@ -2,6 +2,7 @@
 // plain C++ compiler can check them without a GPU.
 #pragma once
 
+#include <math.h>
 #include <stdint.h>
 #include <stdlib.h>
 
@@ -37,18 +38,21 @@ inline int64_t round_tile_bound(int64_t n_items, int64_t group, int64_t chunk, i
 }
 
 // Rows per tile of a screened round.  `chunk` suits rounds that fill the chip;
-// a round whose lists make fewer than `want` tiles of it splits its lists (of
-// the average length) into twice as many equal parts, down to 128 rows, until
-// it does.  25 lists of 2,145 rows at 768 dimensions, 124 queries: 185 us in
-// whole lists, 38 in 256 rows; 20 lists of 1,517 at 96 dimensions: 63 -> 26.
+// lists that make few tiles of it are split (by the average length) into twice
+// as many equal parts, down to 128 rows, as long as nine tenths of the grid's
+// work-groups hold the tiles: a second tile per work-group costs more than the
+// shorter ones save (80 lists of 2,229 rows, fp32 128, loose threshold: 24 us
+// in 160 tiles, 31 in 640).  25 lists of 2,145 rows at 768 dimensions, 124
+// queries: 185 us in whole lists, 45 in 200 tiles; 20 of 1,517 at 96: 63 -> 26.
 // A split is taken only where its tiles fit tile_cap for any lists.
-inline int screen_rows_per_tile(int chunk, int64_t want, int64_t n_items, int64_t group,
+inline int screen_rows_per_tile(int chunk, int64_t grid, int64_t n_items, int64_t group,
                                 int64_t nlist, int64_t n, int64_t max_list, int64_t tile_cap) {
+  const double per = (double)n_items / (double)std::max<int64_t>(nlist, 1);
+  const double lists = std::max((double)nlist * (1.0 - exp(-per)), 1.0);  // that have items
+  const int64_t groups = (int64_t)(lists * ceil((double)n_items / (lists * (double)group)));
   const int64_t avg = std::max<int64_t>(n / std::max<int64_t>(nlist, 1), 1);
-  const int64_t lists = std::max<int64_t>(std::min(n_items, nlist), 1);
-  const int64_t groups = lists * std::max<int64_t>((n_items + lists * group - 1) / (lists * group), 1);
   int64_t parts = (avg + chunk - 1) / chunk;
-  while (groups * parts < want && avg / (2 * parts) >= 128) {
+  while (groups * 2 * parts <= grid * 9 / 10 && avg / (2 * parts) >= 128) {
     parts *= 2;
     const int64_t rows = ((avg + parts - 1) / parts + 63) / 64 * 64;
     if (rows >= chunk) continue;  // the first split of lists just past a chunk

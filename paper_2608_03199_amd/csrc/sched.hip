@@ -91,6 +91,47 @@ __device__ __forceinline__ int group_size(int c, int ntq, int tile_q) {
   return min(gs, tile_q);
 }
 
+// A list's tiles: query tiles x row chunks, tiles that share a row chunk
+// adjacent.
+struct ListTiles {
+  int32_t list, c;      // partition and its items
+  int32_t len;          // its rows (< 2^31, checked at load)
+  int32_t item_begin;   // first item in the bucket
+  int32_t at;           // first tile
+  int64_t r0;           // first row
+};
+// How many: divisions in 32 bits (c, len, row_chunk < 2^31), each a quarter of
+// a 64-bit one's time in the one work-group that all lists wait for.
+__device__ __forceinline__ int64_t tile_count(int32_t c, int32_t len, int32_t row_chunk,
+                                              int32_t tile_q) {
+  if (c <= 0 || len <= 0) return 0;
+  const uint32_t ntq = ((uint32_t)c + (uint32_t)tile_q - 1u) / (uint32_t)tile_q;
+  const uint32_t nch = ((uint32_t)len + (uint32_t)row_chunk - 1u) / (uint32_t)row_chunk;
+  return (int64_t)ntq * nch;
+}
+// Tiles first, first + step, ... of the list's nt.
+__device__ __forceinline__ void put_tiles(const ListTiles& l, int nt, int first, int step,
+                                          int32_t row_chunk, int32_t tile_q,
+                                          Tile* __restrict__ tiles, int64_t tile_cap) {
+  const int ntq = (l.c + tile_q - 1) / tile_q;
+  const int gs = group_size(l.c, ntq, tile_q);
+  for (int i = first; i < nt; i += step) {
+    const int ch = ntq == 1 ? i : i / ntq, tq = i - ch * ntq;
+    Tile t;
+    t.r0 = l.r0 + (int64_t)ch * row_chunk;
+    t.nrows = (int32_t)min<int64_t>(row_chunk, l.len - (int64_t)ch * row_chunk);
+    t.item_begin = l.item_begin + tq * gs;
+    t.nq = min(gs, l.c - tq * gs);
+    t.list = l.list;
+    // past the buffer: reported by the offsets kernel
+    if ((int64_t)l.at + i < tile_cap) tiles[(int64_t)l.at + i] = t;
+  }
+}
+// Lists of more tiles are written by whole waves of the offsets kernel (one
+// store after the other they took 0.2 us a tile: 20 lists of 40 tiles each
+// 12 us a round).
+constexpr int kLaneTiles = 4;
+
 __global__ __launch_bounds__(kOffThreads) void sched_offsets_kernel(
     int32_t* cnt, const int64_t* __restrict__ list_offsets, int32_t nlist,
     int32_t row_chunk, int32_t tile_q, int32_t* __restrict__ item_off,
@@ -102,10 +143,15 @@ __global__ __launch_bounds__(kOffThreads) void sched_offsets_kernel(
   // every list's item count and length (rows < 2^31, checked at load) in
   // LDS: the loads are coalesced and all in flight at once, and each thread
   // then reads its own contiguous range of lists from LDS
-  extern __shared__ int32_t s_lists[];  // [nlist] counts, then [nlist] lengths
+  // [nlist] counts, then [nlist] lengths, then (tiles) up to nlist long lists
+  extern __shared__ __align__(16) int32_t s_lists[];
   int32_t* const s_c = s_lists;
   int32_t* const s_l = s_lists + nlist;
+  ListTiles* const s_long = (ListTiles*)(s_lists + 2 * nlist);
   const int t = threadIdx.x;
+  __shared__ int s_nlong;
+  if (t == 0) s_nlong = 0;
+  int64_t row0 = 0;  // list t's first row
   {
     int32_t cv[kOffPer];
     int64_t a0[kOffPer], a1[kOffPer];
@@ -128,6 +174,7 @@ __global__ __launch_bounds__(kOffThreads) void sched_offsets_kernel(
         s_l[p] = (int32_t)(a1[u] - a0[u]);
       }
     }
+    row0 = a0[0];
   }
   __syncthreads();
   const int per = (nlist + kOffThreads - 1) / kOffThreads;
@@ -135,11 +182,11 @@ __global__ __launch_bounds__(kOffThreads) void sched_offsets_kernel(
   int64_t si = 0, st = 0;
   unsigned long long list_rows = 0, item_rows = 0, loads = 0;
   for (int p = b; p < e; ++p) {
-    const int64_t len = s_l[p];
+    const int32_t len = s_l[p];
     const int c = s_c[p];
     si += c;
     if (c > 0 && len > 0) {
-      st += (int64_t)((c + tile_q - 1) / tile_q) * ((len + row_chunk - 1) / row_chunk);
+      st += tile_count(c, len, row_chunk, tile_q);
       list_rows += (unsigned long long)len;
       item_rows += (unsigned long long)len * (unsigned long long)c;
       loads += 1;
@@ -173,39 +220,25 @@ __global__ __launch_bounds__(kOffThreads) void sched_offsets_kernel(
     }
     all_tiles += wt;
   }
+  if (tiles) {
+    // at most kOffThreads lists (checked by the launch): thread t has list t
+    if (t < nlist) {
+      const ListTiles l = {t, s_c[t], s_l[t], (int32_t)ri, (int32_t)rt, row0};
+      const int nt = (int)st;  // its only list
+      if (nt > kLaneTiles)
+        s_long[atomicAdd(&s_nlong, 1)] = l;
+      else if (nt > 0)
+        put_tiles(l, nt, 0, 1, row_chunk, tile_q, tiles, tile_cap);
+    }
+  }
   for (int p = b; p < e; ++p) {
-    const int64_t len = s_l[p];
     const int c = s_c[p];
     item_off[p] = (int32_t)ri;
     cursor[p] = (int32_t)ri;
     tile_off[p] = (int32_t)rt;
-    if (tiles) {
-      // the tiles of the list, written here (few lists per thread), and the
-      // list's histogram entry cleared for the next round
-      cnt[p] = 0;
-      if (c > 0 && len > 0) {
-        const int ntq = (c + tile_q - 1) / tile_q;
-        const int gs = group_size(c, ntq, tile_q);
-        const int nch = (int)((len + row_chunk - 1) / row_chunk);
-        int32_t o = (int32_t)rt;
-        const int64_t lb = list_offsets[p];
-        for (int ch = 0; ch < nch; ++ch) {
-          for (int tq = 0; tq < ntq; ++tq) {
-            Tile tl;
-            tl.r0 = lb + (int64_t)ch * row_chunk;
-            tl.nrows = (int32_t)min<int64_t>(row_chunk, len - (int64_t)ch * row_chunk);
-            tl.item_begin = (int32_t)ri + tq * gs;
-            tl.nq = min(gs, c - tq * gs);
-            tl.list = p;
-            if (o < tile_cap) tiles[o] = tl;  // past the buffer: reported below
-            ++o;
-          }
-        }
-      }
-    }
+    if (tiles) cnt[p] = 0;  // the list's histogram entry, for the next round
     ri += c;
-    if (c > 0 && len > 0)
-      rt += (int64_t)((c + tile_q - 1) / tile_q) * ((len + row_chunk - 1) / row_chunk);
+    if (p + 1 < e) rt += tile_count(c, s_l[p], row_chunk, tile_q);
   }
   for (int o = 32; o > 0; o >>= 1) {
     list_rows += __shfl_xor(list_rows, o);
@@ -218,6 +251,12 @@ __global__ __launch_bounds__(kOffThreads) void sched_offsets_kernel(
     atomicAdd(&s_stat[2], loads);
   }
   __syncthreads();
+  if (tiles)
+    for (int i = t >> 6; i < s_nlong; i += kOffThreads / 64) {
+      const ListTiles l = s_long[i];
+      put_tiles(l, (int)tile_count(l.c, l.len, row_chunk, tile_q), lane, 64, row_chunk, tile_q,
+                tiles, tile_cap);
+    }
   if (t == 0) {
     // a tile count past the buffer (never, by the host's bound) runs no scan
     // and fails the search
@@ -324,9 +363,8 @@ __global__ __launch_bounds__(kGroupThreads) void sched_scatter_grouped_kernel(
   }
 }
 
-// One thread per list: write its tiles (query tiles x row chunks), tiles that
-// share a row chunk adjacent, and clear the list's histogram entry for the
-// next round.
+// One thread per list: write its tiles and clear the list's histogram entry
+// for the next round.
 __global__ void sched_tiles_kernel(int32_t* __restrict__ cnt, const int32_t* __restrict__ item_off,
                                    const int32_t* __restrict__ tile_off,
                                    const int64_t* __restrict__ list_offsets, int32_t nlist,
@@ -334,27 +372,15 @@ __global__ void sched_tiles_kernel(int32_t* __restrict__ cnt, const int32_t* __r
                                    int64_t tile_cap) {
   const int p = blockIdx.x * blockDim.x + threadIdx.x;
   if (p >= nlist) return;
-  const int c = cnt[p];
+  ListTiles l = {p, cnt[p], 0, 0, 0, 0};
   cnt[p] = 0;
-  const int64_t len = list_offsets[p + 1] - list_offsets[p];
-  if (c == 0 || len == 0) return;
-  const int ntq = (c + tile_q - 1) / tile_q;
-  const int gs = group_size(c, ntq, tile_q);
-  const int nch = (int)((len + row_chunk - 1) / row_chunk);
-  int32_t o = tile_off[p];
-  const int64_t lb = list_offsets[p];
-  for (int ch = 0; ch < nch; ++ch) {
-    for (int tq = 0; tq < ntq; ++tq) {
-      Tile t;
-      t.r0 = lb + (int64_t)ch * row_chunk;
-      t.nrows = (int32_t)min<int64_t>(row_chunk, len - (int64_t)ch * row_chunk);
-      t.item_begin = item_off[p] + tq * gs;
-      t.nq = min(gs, c - tq * gs);
-      t.list = p;
-      if (o < tile_cap) tiles[o] = t;
-      ++o;
-    }
-  }
+  if (l.c == 0) return;
+  l.r0 = list_offsets[p];
+  l.len = (int32_t)(list_offsets[p + 1] - l.r0);
+  l.item_begin = item_off[p];
+  l.at = tile_off[p];
+  put_tiles(l, (int)tile_count(l.c, l.len, row_chunk, tile_q), 0, 1, row_chunk, tile_q, tiles,
+            tile_cap);
 }
 
 __device__ __forceinline__ unsigned long long screened_sum(const RoundCounters* rc) {
@@ -711,7 +737,8 @@ hipError_t launch_sched_offsets(int32_t* cnt, const int64_t* list_offsets, int32
                           hipFuncAttributeMaxDynamicSharedMemorySize, 8 * kMaxNlist);
   if (attr != hipSuccess) return attr;
   if (nlist > kMaxNlist) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(sched_offsets_kernel, dim3(1), dim3(kOffThreads), (size_t)8 * nlist, s, cnt,
+  const size_t lds = (size_t)nlist * (8 + (tiles ? sizeof(ListTiles) : 0));
+  hipLaunchKernelGGL(sched_offsets_kernel, dim3(1), dim3(kOffThreads), lds, s, cnt,
                      list_offsets, nlist, row_chunk, tile_q, item_off, cursor, tile_off, rc, tiles,
                      tile_cap);
   return hipGetLastError();

@@ -50,9 +50,9 @@ int main() {
         const int chunk = screen_rows_per_tile(chunk0, 256, nlist * 100ll, 128, nlist,
                                                (int64_t)nlist * len, len, 1 << 20);
         const int64_t t = (int64_t)nlist * ((len + chunk - 1) / chunk);
-        if (t < 256 && chunk > 320 && len > 320) return 5;
+        if (2 * t < 200 && chunk > 320 && len > 320) return 5;
+        if (t > 256 && chunk < chunk0) return 9;  // one tile per work-group
         if (chunk < 128 && chunk < chunk0) return 6;
-        if (t > 1024 && chunk < 1024 && chunk < chunk0) return 7;  // no more than it needs
       }
   // a round that fills the chip keeps its chunk
   if (screen_rows_per_tile(2048, 512, 65536, 128, 1024, 1000000, 1300, 1 << 20) != 2048) return 8;
