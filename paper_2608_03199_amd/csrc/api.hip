@@ -18,6 +18,7 @@
 #include <string.h>
 
 #include <algorithm>
+#include <functional>
 #include <mutex>
 #include <string>
 #include <vector>
@@ -149,6 +150,7 @@ struct sieve_index {
   // pairs of one list, ascending
   double scr_slack = 0.0;
   std::vector<float> scr_scores;
+  int64_t scr_pairs = 0;  // sampled; scr_scores has the largest quarter
   std::vector<int64_t> h_offsets;
   int64_t max_list = 0;
   double cmax = 0.0;
@@ -233,9 +235,33 @@ double host_elem(const void* base, int dtype, int64_t i) {
   return (double)((const _Float16*)base)[i];
 }
 
-// Rounds of a search are screened while fewer than 1 / kScreenPassInv of
-// their (query, row) pairs pass.
-constexpr unsigned long long kScreenPassInv = 40;
+// A round is screened where fewer than 1 / screen_limit of its (query, row)
+// pairs pass: a passing pair is scored with a gather of its own, 0.15 to 0.5 ns,
+// where the exact scan of a dense round spends 1 to 9 ps on every pair, least on
+// fp16 rows of the dimensions it is compiled for (own_f16).  First rounds of
+// 65,536 and of 4,096 items over 512 lists (dense, sparse), exact / screened us:
+//   fp16  64   dense 1/611: 266/268, 1/120: 123/135, 1/31: 116/195  sparse 1/37: 64/57
+//   fp16 128         1/619: 298/333, 1/251: 100/98,  1/59: 178/255         1/51: 62/52
+//   fp16 768         1/289: 5695/4661, 1/117: 278/761                      1/117: 165/179
+//   fp16  96         1/1304: 86/67, 1/271: 101/103, 1/63: 196/274          1/19: 108/70
+//   fp16 256         1/150: 189/171, 1/20: 423/758                         1/20: 138/111
+//   fp16 512         1/232: 393/179, 1/15: 581/1311                        1/15: 242/201
+//   fp32 128         1/252: 235/124, 1/124: 361/407                        1/14: 113/97
+//   fp32 256         1/150: 598/275, 1/20: 759/1340                        1/20: 269/156
+bool own_f16(int dtype, int d) {
+  return dtype == SIEVE_F16 && vector_frag_bytes(dtype, d, 16) > 0;
+}
+unsigned screen_limit(int dtype, int d, bool dense) {
+  if (!dense) return own_f16(dtype, d) ? 40 : 15;
+  if (own_f16(dtype, d)) return d <= 64 ? 500 : (d <= 128 ? 400 : 150);
+  return dtype == SIEVE_F32 ? 100 : (unsigned)std::max(40, 32000 / d);
+}
+// What ends the screening of a search after a round: the share mostly falls
+// from a dense round to the next ones, which are sparse.
+unsigned screen_limit_after(int dtype, int d, bool dense) {
+  return dense ? std::max(40u, screen_limit(dtype, d, true) * 2 / 5)
+               : screen_limit(dtype, d, false);
+}
 
 enum Phase { kRank = 0, kSched, kScan, kUpdate, kFinal, kTotal, kPhases };
 
@@ -370,6 +396,7 @@ struct SearchPlan {
   int spec_min;        // a line must move at least this far to speculate
   int hit_words;       // 32-bit words per query of the rank bitmap (spec)
   bool screen;         // screened scans (screen_tile.h)
+  bool screen_first;   // in the first round too
   bool screen_forced;  // in every round, however many pairs pass (SIEVE_SCREEN = 2)
   int s_chunk;         // rows per tile in their sparse rounds
   int s_chunk_dense;   // and in their dense rounds
@@ -583,25 +610,25 @@ ScanArgs make_scan_args(sieve_index* ix, const void* queries, const int64_t* exc
   return a;
 }
 
+bool dense_round(const sieve_index* ix, const SearchPlan& pl, int64_t n_items) {
+  return n_items >= (int64_t)pl.dense_q * ix->nlist;
+}
+
 // One scheduling round over n_items ready items (already histogrammed).
 // at: an event recorded at the stream's current position (-1: none), which
 // then opens the schedule span; on return, the event that closes the scan.
 int run_round(sieve_index* ix, const ScanArgs& sa, int n_items, int64_t q0, const int32_t* P,
-              const SearchPlan& pl, hipStream_t s, bool timed, int* at) {
+              const SearchPlan& pl, bool screen, hipStream_t s, bool timed, int* at) {
   RoundCounters* rc = (RoundCounters*)ix->rc.p;
-  const bool dense = (int64_t)n_items >= (int64_t)pl.dense_q * ix->nlist;
+  const bool dense = dense_round(ix, pl, n_items);
   int chunk = dense ? pl.row_chunk_dense : pl.row_chunk;
   int group = pl.group_q, tile_q = pl.tile_q, grid = pl.scan_grid;
   const int64_t tile_cap = (int64_t)(ix->tiles.bytes / sizeof(Tile));
-  if (pl.screen) {
+  if (screen) {
     group = tile_q = screen_tile_q(ix->d, dense);
     grid = ((ix->cus * screen_grid_per_cu(ix->d, dense) + 7) / 8) * 8;
-    // a tile per work-group; where the queries are staged in LDS, one for every
-    // other (128 lists of 781 rows, 768 dimensions, 128 queries each: 43 us in
-    // 128 tiles, 51 in 256)
-    chunk = screen_rows_per_tile(dense ? pl.s_chunk_dense : pl.s_chunk,
-                                 ix->d <= 128 ? grid : grid / 2, n_items, group, ix->nlist, ix->n,
-                                 ix->max_list, tile_cap);
+    chunk = screen_rows_per_tile(dense ? pl.s_chunk_dense : pl.s_chunk, grid, n_items, group,
+                                 ix->nlist, ix->n, ix->max_list, tile_cap);
   } else if (pl.rega) {
     // dense rounds: 128-query tiles of whole lists, one work-group per CU;
     // sparse rounds: 64-query tiles of 512 rows, two per CU
@@ -620,8 +647,8 @@ int run_round(sieve_index* ix, const ScanArgs& sa, int n_items, int64_t q0, cons
                                tile_cap, s));
   HIP_TRY(launch_sched_scatter((const Item*)ix->items.p, n_items, P, pl.n, (int32_t)q0, sa.exclude,
                                (int32_t*)ix->cursor.p, (BItem*)ix->bucket.p,
-                               pl.screen ? (const ScreenParam*)ix->qpar.p : nullptr,
-                               pl.screen ? ix->lpar : nullptr, pl.tau, ix->d, ix->nlist, s));
+                               screen ? (const ScreenParam*)ix->qpar.p : nullptr,
+                               screen ? ix->lpar : nullptr, pl.tau, ix->d, ix->nlist, s));
   if (!fuse)
     HIP_TRY(launch_sched_tiles((int32_t*)ix->cnt.p, (const int32_t*)ix->item_off.p,
                                (const int32_t*)ix->tile_off.p, ix->offsets, ix->nlist, chunk,
@@ -630,7 +657,7 @@ int run_round(sieve_index* ix, const ScanArgs& sa, int n_items, int64_t q0, cons
   ScanArgs sr = sa;
   sr.dynamic = scan_dynamic(ix, n_items, dense, chunk, group, grid);
   sr.tile_q = tile_q;
-  if (pl.screen) {
+  if (screen) {
     ScreenArgs sc;
     (ScanArgs&)sc = sr;
     sc.v8 = ix->v8;
@@ -652,7 +679,7 @@ int run_round(sieve_index* ix, const ScanArgs& sa, int n_items, int64_t q0, cons
     // the round's counters, for the per-round log (sieve_round_log)
     const int slot = (int)ix->round_items.size();
     ix->round_items.push_back(n_items);
-    ix->round_row_bytes.push_back(pl.screen ? 64.0 * screen_chunks(ix->d)
+    ix->round_row_bytes.push_back(screen ? 64.0 * screen_chunks(ix->d)
                                             : (double)ix->d * elem_bytes(ix->dtype));
     ix->round_span.push_back(e1 >= 0 && e2 >= 0 ? (int)ix->span_phase.size() - 1 : -1);
     if (slot < kMaxLogRounds)
@@ -788,7 +815,8 @@ int search_impl(sieve_index* ix, const void* queries, int64_t nq, const int64_t*
           sa.hit_words = pl.hit_words;
           spec_used = true;
         }
-        if ((st = run_round(ix, sa, (int)n_items, 0, P, pl, s, timed, &at))) return st;
+        const bool screened = pl.screen && (rounds > 0 || pl.screen_first);
+        if ((st = run_round(ix, sa, (int)n_items, 0, P, pl, screened, s, timed, &at))) return st;
         const int u0 = at;
         int32_t* have = (int32_t*)ix->have.p;
         int32_t* ext = (int32_t*)ix->ext.p;
@@ -812,15 +840,13 @@ int search_impl(sieve_index* ix, const void* queries, int64_t nq, const int64_t*
         sm.rank_error = rs->rank_error;
         sm.heavy = rs->heavy;
         sm.hits = rs->hits;
-        if (pl.screen && !pl.screen_forced) {
-          // the screen pays while few pairs pass it: a pair scored exactly
-          // costs about 16 pairs of the exact scan's tiles (one pair of a
-          // 16 x 16 product block is used)
-          const unsigned long long scr = rs->screened, rows = rs->item_rows;
-          if ((scr - scr_seen) * kScreenPassInv > rows - rows_seen) pl.screen = false;
-          scr_seen = scr;
-          rows_seen = rows;
-        }
+        if (screened && !pl.screen_forced &&
+            (rs->screened - scr_seen) *
+                    screen_limit_after(ix->dtype, ix->d, dense_round(ix, pl, n_items)) >
+                rs->item_rows - rows_seen)
+          pl.screen = false;
+        scr_seen = rs->screened;
+        rows_seen = rs->item_rows;
         if (rs->sched_error)
           return fail(SIEVE_EINTERNAL, "a round's tiles exceeded the tile buffer");
         items_total += n_items;
@@ -866,9 +892,21 @@ int search_impl(sieve_index* ix, const void* queries, int64_t nq, const int64_t*
         at = mark(ix, timed, s);
         span(ix, kRank, r0, at);
         if (!ix->v8) pl.screen = false;
-        if ((st = run_round(ix, sa, (int)(c * pl.n), q0, P, pl, s, timed, &at))) return st;
+        if ((st = run_round(ix, sa, (int)(c * pl.n), q0, P, pl, pl.screen, s, timed, &at)))
+          return st;
         items_total += c * pl.n;
         ++rounds;
+        if (pl.screen && !pl.screen_forced && q0 == 0 && c < nq) {
+          // the first of several chunks says whether the others are screened
+          HIP_TRY(hipMemcpyAsync(ix->rc_host, rc, sizeof(RoundCounters), hipMemcpyDeviceToHost,
+                                 s));
+          HIP_TRY(hipStreamSynchronize(s));
+          unsigned long long scr = 0;
+          for (unsigned long long x : ix->rc_host->screened) scr += x;
+          if (scr * screen_limit(ix->dtype, ix->d, dense_round(ix, pl, c * pl.n)) >
+              ix->rc_host->item_rows)
+            pl.screen = false;
+        }
       }
       HIP_TRY(hipMemcpyAsync(ix->rc_host, rc, sizeof(RoundCounters), hipMemcpyDeviceToHost, s));
       HIP_TRY(hipStreamSynchronize(s));
@@ -1052,18 +1090,57 @@ int plan_search(const sieve_index* ix, int64_t nq, int32_t k, float tau, int32_t
   if (pl->row_chunk_dense < pl->row_chunk) pl->row_chunk_dense = pl->row_chunk;
   pl->dense_q = env_int("SIEVE_DENSE_Q", 64);
   // Screened scans: where few pairs can pass, by the share of sampled row
-  // pairs of one list whose score is within the slack of tau or above (a
-  // query's first lists are the likes of its own).  The first round is checked
-  // against the same limit as it runs.  SIEVE_SCREEN = 0 turns them off, 2
-  // forces them in every round where the copy exists (tests).
+  // pairs of one list whose score is within the slack of tau or above.  Where
+  // that share hardly grows below tau, the pairs are near duplicates: a query
+  // meets its own in its first list, so a round over s0 ranks has 1 / s0 of
+  // the share (1.3 of it measured: a query shares its list's largest groups),
+  // and the rounds after the first next to none.  Otherwise it passes
+  // at all ranks and in all rounds, a little less at later ones (1/39 sampled:
+  // 1/45 of two ranks, 1/63 of eight, 1/95 of the next round).  SIEVE_SCREEN = 0 turns the screen off, 2 forces it in every round
+  // where the copy exists (tests).
   const int scr = env_count("SIEVE_SCREEN", 1);
   pl->screen = ix->copy_built && scr != 0 && arena_on(ix);
+  pl->screen_first = true;
   pl->screen_forced = scr == 2;
   if (pl->screen && !pl->screen_forced) {
     const auto& v = ix->scr_scores;
-    const float lim = (float)((double)tau - ix->scr_slack);
-    const size_t pass = (size_t)(v.end() - std::lower_bound(v.begin(), v.end(), lim));
-    if (v.empty() || pass * kScreenPassInv > v.size()) pl->screen = false;
+    auto share = [&](double t) {
+      const auto it = std::lower_bound(v.begin(), v.end(), (float)(t - ix->scr_slack));
+      return (double)(v.end() - it) / (double)std::max<int64_t>(ix->scr_pairs, 1);
+    };
+    const double at_tau = share(tau);
+    const bool near_dups = share(tau - 0.1 * fabs(tau)) <= 1.5 * at_tau;
+    const int s0 = mode == 0 ? std::min(W, pl->n) : (mode == 1 ? 1 : pl->n);
+    const double first = near_dups ? 1.3 * at_tau / std::min(s0, 64) : 0.9 * at_tau;
+    const int64_t items = std::max<int64_t>(nq * s0, 1);
+    const bool dense = dense_round(ix, *pl, items), own = own_f16(ix->dtype, ix->d);
+    // (near duplicates crowd into few tiles: fp16 64, 1,330 items on 84 lists,
+    // 1/237: 27 us exact, 42 screened)
+    const unsigned limit = screen_limit(ix->dtype, ix->d, dense || (near_dups && own));
+    pl->screen_first = first * limit < 1.0;
+    // Large groups of near duplicates end in few tiles, which a round of few
+    // tiles per work-group waits for (fp16 768: 872 items on 59 lists of 873
+    // rows 33 us exact, 46 screened; 41,208 on 136 lists of 561 rows 130, 225).
+    // Up to 128 dimensions the exact scan's tiles are whole lists in a dense
+    // round, and the screen's are not (4,755 items on 28 lists of 1,932 rows:
+    // 602 us exact, 96).
+    const int64_t tq = screen_tile_q(ix->d, true);
+    const int64_t touched = std::min<int64_t>(items, ix->nlist);
+    const int64_t tiles = touched * ((items + touched * tq - 1) / (touched * tq));
+    if (ix->d <= 128) {
+      if (dense && tiles < ix->cus) pl->screen_first = true;
+    } else if (near_dups && at_tau > 0.01 && own &&
+               tiles < 4 * ix->cus * screen_grid_per_cu(ix->d, true)) {
+      pl->screen_first = false;
+    }
+    const double most = !near_dups ? 0.25 : (own ? (mode == 2 ? 0.025 : 0.05) : 0.1);
+    // The rounds after an exact first one are worth the queries' 8-bit copies
+    // where rows come from memory, or the exact scan is slow (fp16 128, 1,398
+    // queries on 65,000 rows: 264 us without the copies, 277).
+    const bool cheap = own && ix->n * ix->d * 2 < (64ll << 20);
+    if (v.empty() || at_tau >= most ||
+        (!pl->screen_first && (!near_dups || mode == 2 || cheap)))
+      pl->screen = false;
   }
   {
     // register-held queries take whole lists in dense rounds, like the exact
@@ -1103,7 +1180,7 @@ int plan_search(const sieve_index* ix, int64_t nq, int32_t k, float tau, int32_t
   if (pl->rank_chunk < 1) pl->rank_chunk = 1;
   if (mode == 2) {
     int64_t fc = (int64_t)(64ll << 20) / pl->n;  // <= 64M items per chunk
-    if (fc < 1) fc = 1;
+    fc = env_int("SIEVE_FIX_CHUNK", (int)std::max<int64_t>(fc, 1));  // (queries; tests)
     pl->fix_chunk = nq < fc ? nq : fc;
     if (pl->fix_chunk < 1) pl->fix_chunk = 1;
     pl->item_cap = pl->fix_chunk * pl->n;
@@ -1295,9 +1372,15 @@ SIEVE_API int sieve_load_index(const void* vectors, int32_t dtype, int64_t n, in
       }
     if (lists > 0) {
       ix->scr_slack = 2.0 * (err / (double)lists) * (norm / (double)lists);
+      auto& v = ix->scr_scores;
       for (float x : hs)
-        if (x > -INFINITY) ix->scr_scores.push_back(x);  // (NaN left out)
-      std::sort(ix->scr_scores.begin(), ix->scr_scores.end());
+        if (x > -INFINITY) v.push_back(x);  // (NaN left out)
+      ix->scr_pairs = (int64_t)v.size();
+      // the largest quarter: where more pass, the screen is off anyway
+      const size_t keep = v.size() / 4;
+      std::nth_element(v.begin(), v.begin() + keep, v.end(), std::greater<float>());
+      v.resize(keep);
+      std::sort(v.begin(), v.end());
     }
   }
   if (!isfinite(ix->cmax)) return bail(fail(SIEVE_EINVAL, "centroids contain inf or NaN"));

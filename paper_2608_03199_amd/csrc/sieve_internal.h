@@ -292,7 +292,7 @@ hipError_t launch_index_rows(int dtype, int d, const void* vectors, const int64_
                              void* frag, void* v8, ScreenParam* lpar, hipStream_t s);
 // Scores of row pairs inside kScreenSample lists ([kScreenSample * 256], -inf
 // in unused places).
-constexpr int kScreenSample = 32;
+constexpr int kScreenSample = 128;
 hipError_t launch_screen_sample(int d, const void* v8, const int64_t* offsets,
                                 const int64_t* frag_offsets, int32_t nlist,
                                 const ScreenParam* lpar, float* out, hipStream_t s);

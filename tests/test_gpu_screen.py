@@ -150,3 +150,78 @@ def test_screen_underflowing_products(scale):
     q = torch.cat([v[sel], -v[sel], v[sel].flip(1)]).contiguous()
     _check(ix, q, ids[sel].repeat(3).contiguous(), 5, 0.0)
     _check(ix, q, ids[sel].repeat(3).contiguous(), 64, scale * scale / 2)
+
+
+# The default setting: which rounds are screened is a rule on the data, the outputs are not.
+def _grouped(n_lists, per, d, group, seed):
+    """Lists of `per` rows, the first `group` of each near duplicates of one another."""
+    import paper_2608_03199_amd as ps
+    g = torch.Generator().manual_seed(seed)
+    c = torch.nn.functional.normalize(torch.randn(n_lists, d, generator=g), dim=1)
+    v = torch.nn.functional.normalize(
+        c[:, None] + 2.0 * torch.randn(n_lists, per, d, generator=g) / d ** 0.5, dim=2)
+    if group > 1:
+        v[:, 1:group] = torch.nn.functional.normalize(
+            v[:, :1] + 0.05 * torch.randn(n_lists, group - 1, d, generator=g) / d ** 0.5, dim=2)
+        v = torch.stack([x[torch.randperm(per, generator=g)] for x in v])
+    v = v.reshape(-1, d).half().cuda()
+    off = torch.arange(0, n_lists * per + 1, per).cuda()
+    ids = torch.arange(len(v)).cuda()
+    return ps.Index(v, off, ids, c.half().cuda()), v, ids
+
+
+def test_default_screens_no_crowded_first_round():
+    # 1/9 of a list's row pairs are near duplicates: exact; 1/40: the first round exact, the
+    # rest screened (rows from memory); none: all rounds screened
+    seen = {}
+    for group in (100, 40, 1):
+        ix, v, ids = _grouped(1024, 300, 128, group, group)
+        sel = torch.arange(0, len(v), 37).cuda()
+        q, ex = v[sel].contiguous(), ids[sel].contiguous()
+        got = ix.search(q, ex, 10, 0.9, 2, 64, with_stats=True)
+        seen[group] = _screened(ix)
+        with knobs(SIEVE_SCREEN=0):
+            _same(got[:3], ix.search(q, ex, 10, 0.9, 2, 64))
+        ix.close()
+    assert not any(seen[100])
+    assert not seen[40][0] and all(seen[40][1:]) and len(seen[40]) > 1
+    assert all(seen[1])
+
+
+def test_default_stops_screening_between_rounds():
+    # queries unlike the rows sampled at load: all their pairs pass from the first round on,
+    # and the rounds after it are exact
+    ix, v, ids = _grouped(256, 300, 128, 1, 5)
+    q = (8.0 * v[::300]).contiguous()
+    got = ix.search(q, None, 10, 0.9, 2, 64, with_stats=True)
+    rounds = _screened(ix)
+    assert rounds[0] and len(rounds) > 1 and not any(rounds[1:])
+    with knobs(SIEVE_SCREEN=0):
+        _same(got[:3], ix.search(q, None, 10, 0.9, 2, 64))
+
+
+def test_default_stops_screening_between_fixed_chunks():
+    ix, v, ids = _grouped(256, 300, 128, 1, 5)
+    few = (8.0 * v[::300]).contiguous()
+    with knobs(SIEVE_FIX_CHUNK=100):
+        got = ix.search_fixed(few, None, 10, 0.9, 64, with_stats=True)
+        rounds = _screened(ix)
+        assert rounds == [True, False, False]
+        ix.search_fixed(v[::300].contiguous(), None, 10, 0.9, 64, with_stats=True)
+        assert all(_screened(ix)) and len(_screened(ix)) == 3
+    with knobs(SIEVE_SCREEN=0):
+        _same(got[:3], ix.search_fixed(few, None, 10, 0.9, 64))
+
+
+# The item scatter by groups of 4,096 (at least 32,768 items on at most 2,048 lists), against
+# the exact search with one item at a time (fewer than 32,768 in a round)
+@pytest.mark.parametrize("n_lists,nq,W", [(16, 4100, 8), (2048, 4097, 8), (1, 33000, 1),
+                                          (2049, 4097, 8), (700, 4096, 8), (700, 4095, 8)])
+def test_grouped_item_scatter(n_lists, nq, W):
+    ix, v, ids = _grouped(n_lists, 20, 64, 3, nq)
+    sel = (torch.arange(nq) * 7919 % len(v)).cuda()
+    q, ex = v[sel].contiguous(), ids[sel].contiguous()
+    got = ix.search(q, ex, 5, 0.8, W, 32)
+    for a in range(0, nq, 1000):
+        part = ix.search(q[a:a + 1000].contiguous(), ex[a:a + 1000].contiguous(), 5, 0.8, W, 32)
+        _same([x[a:a + 1000] for x in got], part)
