@@ -664,10 +664,8 @@ int run_round(sieve_index* ix, const ScanArgs& sa, int n_items, int64_t q0, cons
     sc.q8 = ix->q8.p;
     sc.dtype = ix->dtype;
     sc.thr_unit = thr_unit(ix->d);
-    // the spill buffer's share of each work-group (an even entry count)
-    while (sc.spill_cap > 0 &&
-           (size_t)grid * arena_block_entries(sc.spill_cap) * sizeof(TileSpill) > ix->spill.bytes)
-      sc.spill_cap = sc.spill_cap / 4 * 2;
+    if ((size_t)grid * arena_block_entries(sc.spill_cap) * sizeof(TileSpill) > ix->spill.bytes)
+      return fail(SIEVE_EINTERNAL, "the arena's extension is smaller than its grid needs");
     HIP_TRY(launch_screen_scan(sc, grid, s));
   } else
     HIP_TRY(launch_scan(ix->dtype, sr, grid, s));

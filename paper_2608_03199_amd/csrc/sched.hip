@@ -460,7 +460,7 @@ __device__ __forceinline__ void lookahead_one(int64_t q, const int32_t* __restri
     if (reach <= s) return;
     const int e0 = min(s, hv), e1 = min(reach, hv);  // emitted so far / after this update
     if (e1 > e0) {
-      // ranks [e0, e1) are emitted by the caller, after one claim per wave
+      // ranks [e0, e1) are emitted by the caller, after one claim per work-group
       *emit_from = e0;
       *emit_n = e1 - e0;
       if (issued) issued[q] = e1;

@@ -225,8 +225,7 @@ __global__ __launch_bounds__(64) void screen_sample_kernel(
 }
 
 // 16 lanes per query, 16 dimensions per lane and step.  The search's resets
-// (f) ride along, which saves their launch (one query 131 -> 129 us, 100
-// queries on 1M x 768 350 -> 316).
+// (f) ride along, which saves their launch.
 template <int DT>
 __global__ __launch_bounds__(256) void screen_queries_kernel(const char* __restrict__ queries,
                                                              int64_t nq, int32_t d, int32_t nc,
