@@ -663,7 +663,6 @@ int run_round(sieve_index* ix, const ScanArgs& sa, int n_items, int64_t q0, cons
     sc.v8 = ix->v8;
     sc.q8 = ix->q8.p;
     sc.dtype = ix->dtype;
-    sc.thr_unit = thr_unit(ix->d);
     if ((size_t)grid * arena_block_entries(sc.spill_cap) * sizeof(TileSpill) > ix->spill.bytes)
       return fail(SIEVE_EINTERNAL, "the arena's extension is smaller than its grid needs");
     HIP_TRY(launch_screen_scan(sc, grid, s));
@@ -1046,9 +1045,10 @@ int search_impl(sieve_index* ix, const void* queries, int64_t nq, const int64_t*
 
 // mode: 0 lookahead (Algorithm 2), 1 basic (Algorithm 1), 2 fixed probing.
 // speculative: with mode 0, also issue ranks past the stop line (see
-// launch_update_lookahead); outputs are the same either way.
+// launch_update_lookahead); outputs are the same either way.  nidx: indexes that
+// the same queries search in the call.
 int plan_search(const sieve_index* ix, int64_t nq, int32_t k, float tau, int32_t W,
-                int32_t nprobe, int mode, bool speculative, SearchPlan* pl) {
+                int32_t nprobe, int mode, bool speculative, SearchPlan* pl, int nidx = 1) {
   pl->n = nprobe < ix->nlist ? nprobe : ix->nlist;
   if (pl->n > kMaxRanks)
     return fail(SIEVE_EUNSUPPORTED, "min(nprobe, nlist) = %d exceeds %d", pl->n, kMaxRanks);
@@ -1092,9 +1092,11 @@ int plan_search(const sieve_index* ix, int64_t nq, int32_t k, float tau, int32_t
   // that share hardly grows below tau, the pairs are near duplicates: a query
   // meets its own in its first list, so a round over s0 ranks has 1 / s0 of
   // the share (1.3 of it measured: a query shares its list's largest groups),
-  // and the rounds after the first next to none.  Otherwise it passes
-  // at all ranks and in all rounds, a little less at later ones (1/39 sampled:
-  // 1/45 of two ranks, 1/63 of eight, 1/95 of the next round).  SIEVE_SCREEN = 0 turns the screen off, 2 forces it in every round
+  // the rounds after the first next to none, and of nidx indexes one has the
+  // query's group (eight shards, 1/104 sampled: 1/4029 of eight ranks).
+  // Otherwise it passes at all ranks and in all rounds, a little less at later
+  // ones (1/39 sampled: 1/45 of two ranks, 1/63 of eight, 1/95 of the next
+  // round).  SIEVE_SCREEN = 0 turns the screen off, 2 forces it in every round
   // where the copy exists (tests).
   const int scr = env_count("SIEVE_SCREEN", 1);
   pl->screen = ix->copy_built && scr != 0 && arena_on(ix);
@@ -1109,7 +1111,7 @@ int plan_search(const sieve_index* ix, int64_t nq, int32_t k, float tau, int32_t
     const double at_tau = share(tau);
     const bool near_dups = share(tau - 0.1 * fabs(tau)) <= 1.5 * at_tau;
     const int s0 = mode == 0 ? std::min(W, pl->n) : (mode == 1 ? 1 : pl->n);
-    const double first = near_dups ? 1.3 * at_tau / std::min(s0, 64) : 0.9 * at_tau;
+    const double first = near_dups ? 1.3 * at_tau / (std::min(s0, 64) * nidx) : 0.9 * at_tau;
     const int64_t items = std::max<int64_t>(nq * s0, 1);
     const bool dense = dense_round(ix, *pl, items), own = own_f16(ix->dtype, ix->d);
     // (near duplicates crowd into few tiles: fp16 64, 1,330 items on 84 lists,
@@ -1779,7 +1781,7 @@ SIEVE_API int sieve_search_multi(const sieve_index* const* idxs, int32_t nidx,
   for (int32_t i = 0; i < nidx; ++i) {
     sieve_index* ix = const_cast<sieve_index*>(idxs[i]);
     if ((st = plan_search(ix, nq, k, tau, W, nprobe_max, lookahead_mode(lookahead),
-                          lookahead == SIEVE_LOOKAHEAD_SPECULATIVE, &plans[i])))
+                          lookahead == SIEVE_LOOKAHEAD_SPECULATIVE, &plans[i], nidx)))
       return st;
     if (lookahead == SIEVE_LOOKAHEAD_SERIAL) {
       plans[i].group_q = 1;

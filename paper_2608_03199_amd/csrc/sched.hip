@@ -129,8 +129,10 @@ __device__ __forceinline__ void put_tiles(const ListTiles& l, int nt, int first,
 }
 // Lists of more tiles are written by whole waves of the offsets kernel (one
 // store after the other they took 0.2 us a tile: 20 lists of 40 tiles each
-// 12 us a round).
+// 12 us a round), where they are few (a wave takes 0.6 us a list: 512 lists of
+// 7 tiles 20 us).
 constexpr int kLaneTiles = 4;
+constexpr int kLongLists = 64;
 
 __global__ __launch_bounds__(kOffThreads) void sched_offsets_kernel(
     int32_t* cnt, const int64_t* __restrict__ list_offsets, int32_t nlist,
@@ -220,17 +222,14 @@ __global__ __launch_bounds__(kOffThreads) void sched_offsets_kernel(
     }
     all_tiles += wt;
   }
-  if (tiles) {
-    // at most kOffThreads lists (checked by the launch): thread t has list t
-    if (t < nlist) {
-      const ListTiles l = {t, s_c[t], s_l[t], (int32_t)ri, (int32_t)rt, row0};
-      const int nt = (int)st;  // its only list
-      if (nt > kLaneTiles)
-        s_long[atomicAdd(&s_nlong, 1)] = l;
-      else if (nt > 0)
-        put_tiles(l, nt, 0, 1, row_chunk, tile_q, tiles, tile_cap);
-    }
-  }
+  // tiles: at most kOffThreads lists (checked by the launch), thread t has list t
+  const ListTiles mine = {t, t < nlist ? s_c[t] : 0, t < nlist ? s_l[t] : 0, (int32_t)ri,
+                          (int32_t)rt, row0};
+  const int nt_mine = tiles && t < nlist ? (int)st : 0;
+  if (nt_mine > kLaneTiles)
+    s_long[atomicAdd(&s_nlong, 1)] = mine;
+  else if (nt_mine > 0)
+    put_tiles(mine, nt_mine, 0, 1, row_chunk, tile_q, tiles, tile_cap);
   for (int p = b; p < e; ++p) {
     const int c = s_c[p];
     item_off[p] = (int32_t)ri;
@@ -251,12 +250,15 @@ __global__ __launch_bounds__(kOffThreads) void sched_offsets_kernel(
     atomicAdd(&s_stat[2], loads);
   }
   __syncthreads();
-  if (tiles)
+  if (s_nlong <= kLongLists) {
     for (int i = t >> 6; i < s_nlong; i += kOffThreads / 64) {
       const ListTiles l = s_long[i];
       put_tiles(l, (int)tile_count(l.c, l.len, row_chunk, tile_q), lane, 64, row_chunk, tile_q,
                 tiles, tile_cap);
     }
+  } else if (nt_mine > kLaneTiles) {
+    put_tiles(mine, nt_mine, 0, 1, row_chunk, tile_q, tiles, tile_cap);
+  }
   if (t == 0) {
     // a tile count past the buffer (never, by the host's bound) runs no scan
     // and fails the search
@@ -749,7 +751,7 @@ hipError_t launch_sched_scatter(const Item* items, int32_t n_items, const int32_
                                 BItem* bucket, const ScreenParam* qpar, const ScreenParam* lpar,
                                 float tau, int32_t d, int32_t nlist, hipStream_t s) {
   if (n_items <= 0) return hipSuccess;
-  const int32_t unit = qpar ? thr_unit(d) : 0;
+  const int32_t unit = qpar ? thr_unit(screen_chunks(d)) : 0;
   // worth it where a group holds several items of a list
   if (n_items >= 8 * kGroupItems && nlist <= kGroupItems / 2) {
     hipLaunchKernelGGL(sched_scatter_grouped_kernel,

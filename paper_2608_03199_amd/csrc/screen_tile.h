@@ -391,7 +391,7 @@ __global__ __launch_bounds__(kNT, kOcc) void screen_scan_kernel(ScreenArgs a) {
     if ((int)threadIdx.x < kTQ) {
       const bool real = (int)threadIdx.x < r.nq;
       s_init[set][threadIdx.x] =
-          real ? -((it.rank >> kThrShift) * (1 << a.thr_unit)) : kInitNever;
+          real ? -((it.rank >> kThrShift) * (1 << thr_unit(NC))) : kInitNever;
       if (real) {
         s_q[set][threadIdx.x] = it.q;
         s_rank[set][threadIdx.x] = it.rank & (kMaxRanks - 1);

@@ -35,14 +35,15 @@ struct BItem {
 
 // A screened item's threshold, the smallest 8-bit product that may reach tau,
 // is kept beside the rank (< kMaxRanks = 2^kThrShift) as a signed number of 21
-// bits in units of 2^thr_unit(d), rounded down: 127^2 d <= 2^(20 + unit), so
-// the smallest value admits every product, and the rounding is at most 16 of
-// 16.5 million (d = 1,024).  The items take 16 bytes in every kind of round.
+// bits in units of 2^thr_unit, rounded down: 127^2 d <= 2^(20 + unit) for the
+// d = 64 chunks dimensions of a padded row, so the smallest value admits every
+// product, and the rounding is at most 16 of 16.5 million (d = 1,024).  The
+// items take 16 bytes in every kind of round.
 constexpr int kThrShift = 11;
 constexpr int32_t kThrMax = (1 << 20) - 1;  // and -kThrMax - 1 at least
-__host__ __device__ inline int thr_unit(int d) {
+__host__ __device__ constexpr int thr_unit(int chunks) {
   int u = 0;
-  while ((int64_t)127 * 127 * d > ((int64_t)1 << (20 + u))) ++u;
+  while ((int64_t)127 * 127 * 64 * chunks > ((int64_t)1 << (20 + u))) ++u;
   return u;
 }
 
@@ -223,7 +224,6 @@ struct ScreenArgs : ScanArgs {
   const void* v8 = nullptr;
   const void* q8 = nullptr;
   int32_t dtype = 0;
-  int32_t thr_unit = 0;  // of the items' thresholds
 };
 
 // Query rows per tile for a dtype and dimension: as many 16-row blocks (<= 8)
