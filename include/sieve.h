@@ -139,7 +139,12 @@ typedef struct sieve_stats {
  * scan handles at compile time (fp16 64/128/768, fp32 64/128) a second copy in
  * MFMA fragment order (each list padded to whole 16-row blocks), about twice
  * the vectors' bytes in all; the centroids get a fragment-order copy too for
- * the ranking kernels' compile-time dimensions (fp16 128/768, fp32 64/128).
+ * the ranking kernels' compile-time dimensions (fp16 128/256/384/512/768,
+ * fp32 64/128).  For d <= 1024 also an 8-bit copy of the vectors, where it
+ * takes at most a third of the free memory: searches return the same without
+ * it, an allocation of the library that does not fit takes it back (that of
+ * its own index first, then those no search is reading), and with
+ * SIEVE_SCREEN=0 in the environment the load takes none.
  * An allocation failure returns SIEVE_ENOMEM.
  * Synchronous: returns once the copies are complete.
  */
